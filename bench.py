@@ -418,7 +418,7 @@ def bench_fused(args, torch, synth, tr, dev):
                        "images": w.B, "tokens": rows, "D": w.D, "Dc": Dc, "hidden": Hd},
             "unfused": {"ms_per_step": round(t_u * 1e3, 5), "value": round(w.B / t_u, 1),
                         "what": "library GEMM (torch.matmul) + tr_reduce reading X_pre and X_post"},
-            "roofline": {"kernel": "gemm_wide_kernel<cos epilogue> + cos_finish", "bound": "mfma",
+            "roofline": {"kernel": "gemm_large_kernel<cos epilogue> + cos_finish", "bound": "mfma",
                          "achieved": round(flops / t_gemm / 1e12, 1), "avg_launch_ms": round(t_gemm * 1e3, 5),
                          "peak": 2500.0, "unit": "TFLOP/s", "frac": round(flops / t_gemm / 1e12 / 2500.0, 4),
                          "traffic": None, "algorithmic_flops_per_launch": flops,
@@ -459,7 +459,7 @@ def bench_fused(args, torch, synth, tr, dev):
                        "images": w.B, "tokens": rows, "D": w.D, "kept": sk, "Nout": nout},
             "unfused": {"ms_per_step": round(t_u * 1e3, 5), "value": round(w.B / t_u, 1),
                         "what": "tr_reduce (gathered copy) + library GEMM (torch.matmul)"},
-            "roofline": {"kernel": "gemm_wide_kernel<row gather>", "bound": "mfma",
+            "roofline": {"kernel": "gemm_large_kernel<row gather>", "bound": "mfma",
                          "achieved": round(flops / t_gemm / 1e12, 1), "avg_launch_ms": round(t_gemm * 1e3, 5),
                          "peak": 2500.0, "unit": "TFLOP/s", "frac": round(flops / t_gemm / 1e12 / 2500.0, 4),
                          "traffic": None, "algorithmic_flops_per_launch": flops,

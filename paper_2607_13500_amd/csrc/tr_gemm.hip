@@ -12,33 +12,24 @@
 //     sums use C as stored (rounded to bf16), so the score is Eq. (6) on the
 //     x'' the caller receives, as an unfused scoring pass would compute it.
 //
-// Two tilings for gfx950 (64-wide wavefronts, 32x32x16 bf16 MFMA), both with
+// Two kernels for gfx950 (64-wide wavefronts, 32x32x16 bf16 MFMA), both with
 // the same per-element MFMA sequence (k ascending in steps of 16), so they give
 // bit-identical C:
-//   * wide (N % 256 == 0, K % 128 == 0): workgroup tile (64 MT) x 256 x 64
-//     with MT = 4, 3 or 2 picked per shape so the tiles fill the CUs in whole
-//     waves; eight wavefronts in a 2 x 4 grid, each owning 32 MT x 64 of C
-//     (MT x 2 MFMA tiles, 32 MT fp32 accumulators a lane).
-//     Operands go from global memory straight into LDS (buffer loads with the
-//     LDS-destination form, 16 bytes a lane), two LDS stages of 64 KB, so the
-//     next k-tile streams in while the current one feeds the MFMAs with no
-//     staging registers.  LDS rows are 128 bytes with the 16-byte chunks
-//     XOR-swizzled by (row / 2) % 8, which keeps the fragment reads of any 16
-//     consecutive rows on distinct banks.  Buffer range checking reads rows
-//     past the end of A (or invalid gathered rows) as zeros.  The cosine
-//     epilogue stages its block of P through the freed LDS stages.
-//   * narrow (every other shape, or operands beyond 31-bit buffer offsets):
-//     workgroup tile 256 x 128 x 64, four wavefronts of 128 x 64, rows padded
-//     from 128 to 144 bytes for conflict-free fragment reads, the next k-tile
+//   * large: workgroup tile (64 MT) x 256 x 64 with MT = 4, 3 or 2 picked per
+//     shape so the tiles fill the CUs in whole waves, operands straight from
+//     global memory into LDS; described at the kernel.
+//   * narrow (operands beyond 31-bit buffer offsets): workgroup tile 256 x 128
+//     x 64 with 64-bit addresses, four wavefronts of 128 x 64, rows padded from
+//     128 to 144 bytes for conflict-free fragment reads, the next k-tile
 //     prefetched into registers (54 KB of LDS: two workgroups fit a CU).
-// Both use an XCD-aware tile order: workgroup b runs on XCD b % 8; each XCD
-// takes a contiguous run of output tiles with the N tile fastest, so the
-// workgroups sharing an A block-row share that XCD's L2.
+// Both spread the output tiles over the XCDs (workgroup b runs on XCD b % 8)
+// so that the workgroups sharing operand rows share an XCD's L2.
 //
 // MFMA operand layout (32x32x16 bf16, verified on the device): lane l holds
 // A row l % 32 and B column l % 32, k = (l / 32) * 8 .. + 8; accumulator
 // element v of lane l is C[(v / 4) * 8 + (l / 32) * 4 + v % 4][l % 32].
 #include <cstdlib>
+#include <type_traits>
 
 #include "tr_internal.h"
 #include "tr_wave.h"
@@ -60,13 +51,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 
-// bf16 round-to-nearest-even of an fp32 value (finite inputs; NaN stays NaN).
-__device__ __forceinline__ uint16_t to_bf16(float f)
-{
-    const uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-}
+// bf16 round-to-nearest-even of an fp32 value (NaN stays NaN), in hardware.
+__device__ __forceinline__ uint16_t to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 template <bool GATHER, bool COS>
 __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a)
@@ -227,107 +213,281 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a)
     }
 }
 
-// ---- wide tiling -----------------------------------------------------------
-constexpr int kWBN = 256;
-constexpr int kWThreads = 512;
-constexpr int kWStage = kBM * kBK * 2;              // one operand k-tile: 256 rows x 128 B
-constexpr int kWRed = 4 * kBM * 3;                  // cosine partials of the four N-quarters (floats)
+// ---- tiles fed through LDS by LDS-destination loads -------------------------
 constexpr uint32_t kBufWord3 = 0x00020000u;        // raw buffer resource, 32-bit elements
 constexpr uint32_t kBadRow = 0x80000000u;          // a buffer offset past every resource
+constexpr int kSlot = 16384;                       // 128 rows of one k-tile (64 bf16 each)
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));   // 16 bytes at any element
 typedef __attribute__((address_space(3))) unsigned char lds_t;
 typedef __attribute__((address_space(3))) bf16x8 lds_frag;
-typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) bf16x4 lds_quad;
+typedef __attribute__((address_space(3))) u32x4 lds_chunk;
+typedef __attribute__((address_space(3))) float lds_f32;
 
-// MT: MFMA tiles per wavefront along M (4, 3 or 2), so the workgroup tile is
-// 64 MT rows by 256 columns.
-template <int MT, bool GATHER, bool COS>
-__global__ __launch_bounds__(kWThreads, 1) void gemm_wide_kernel(GemmArgs a)
+// Buffer resource over `bytes` bytes at p (wave-uniform); loads past it read 0.
+__device__ __forceinline__ u32x4 buffer_of(const void* p, int64_t bytes)
 {
-    constexpr int BMW = 64 * MT;
-    __shared__ __attribute__((aligned(1024))) unsigned char sA0[kWStage], sA1[kWStage], sB0[kWStage], sB1[kWStage];
-    __shared__ float red[COS ? kWRed : 1];
-    lds_t* const a0 = (lds_t*)sA0;
-    lds_t* const a1 = (lds_t*)sA1;
-    lds_t* const b0 = (lds_t*)sB0;
-    lds_t* const b1 = (lds_t*)sB1;
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    u32x4 r;
+    r.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    r.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu));
+    r.z = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)(bytes < (int64_t)kBadRow ? (uint32_t)bytes : kBadRow - 1u));
+    r.w = kBufWord3;
+    return r;
+}
 
-    const int mt = (a.M + BMW - 1) / BMW, nt = a.N / kWBN;
-    const int tiles = mt * nt;
-    const int per_xcd = (tiles + kXcds - 1) / kXcds;
+// 16 bytes a lane from the buffer straight into LDS at lds + 16 lane.  Written
+// as an instruction (it has no register result) so that the compiler does not
+// tie it to every later LDS read: the kernels below count the loads in flight
+// themselves and wait for exactly those a barrier is about to publish.
+__device__ __forceinline__ void load_lds(u32x4 r, uint32_t lds, uint32_t voff, uint32_t soff)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory");
+}
+
+// At most n of this wavefront's loads still in flight.
+template <int n>
+__device__ __forceinline__ void wait_loads()
+{
+    static_assert(n >= 0 && n < 64, "vmcnt is six bits");
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(n) : "memory");
+}
+
+// This wavefront's LDS reads have returned.
+__device__ __forceinline__ void wait_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Workgroup barrier alone: no wait for memory, nothing scheduled across it.
+__device__ __forceinline__ void barrier()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+__device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c)
+{
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), c, false);
+}
+
+// Sum over each group of eight lanes, in every lane of the group.
+__device__ __forceinline__ float sum8(float x)
+{
+    auto dpp = [](float v, auto ctrl) {
+        return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(
+            0, (int)__float_as_uint(v), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    x += dpp(x, std::integral_constant<int, 0xB1>{});    // lane ^ 1
+    x += dpp(x, std::integral_constant<int, 0x4E>{});    // lane ^ 2
+    x += dpp(x, std::integral_constant<int, 0x141>{});   // 7 - lane within the eight
+    return x;
+}
+
+// Output tile of workgroup b: XCD b % 8 takes a contiguous run of tiles, and
+// the run walks blocks of kTileRows tile rows column by column, so the tiles
+// an XCD works on at once form a block of few rows and few columns and share
+// both operands in its L2.  8192^3, 256 x 256 tiles: 837 -> 792 us against
+// rows of tiles (the operands alone took 757 us to load there).
+constexpr int kTileRows = 4;
+
+__device__ __forceinline__ bool tile_of(int mt, int nt, int& tm, int& tn)
+{
+    const int tiles = mt * nt, per_xcd = (tiles + kXcds - 1) / kXcds;
     const int t = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
-    if (t >= tiles) return;   // whole workgroup leaves together
-    const int m0 = (t / nt) * BMW, n0 = (t % nt) * kWBN;
+    if (t >= tiles) return false;
+    const int group = t / (kTileRows * nt), in = t % (kTileRows * nt);
+    const int rows = mt - group * kTileRows < kTileRows ? mt - group * kTileRows : kTileRows;
+    tm = group * kTileRows + in % rows;
+    tn = in / rows;
+    return true;
+}
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = w >> 2, wn = w & 3;   // 2 x 4 wavefront grid
-
-    // ---- global -> LDS.  Wavefront w fills row blocks MT w .. MT w + MT-1 of
-    // the A tile and 4w .. 4w+3 of the B tile (blocks of 8 rows of 128 B);
-    // lane l writes physical chunk l % 8 of row l / 8 of a block, which holds
-    // logical chunk (l % 8) ^ ((row / 2) % 8).
-    // Offsets are 32-bit bytes from the resource base; the k offset of a
-    // k-tile is the scalar offset.  The host routes larger operands to the
-    // narrow kernel.
-    const uint16_t* A = reinterpret_cast<const uint16_t*>(a.A);
-    const uint16_t* B = reinterpret_cast<const uint16_t*>(a.B);
-    int64_t a_bytes;
-    const uint16_t* abase;
-    if constexpr (GATHER) {
-        abase = A;
-        a_bytes = a.arow_count * a.lda * 2;
-    } else {
-        abase = A + (int64_t)m0 * a.lda;
-        a_bytes = (int64_t)(a.M - m0) * a.lda * 2;
-    }
-    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)abase, (short)0, (int)(a_bytes < (int64_t)kBadRow ? a_bytes : (int64_t)kBadRow - 1), kBufWord3);
-    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(B + (int64_t)n0 * a.ldb), (short)0, (int)(kWBN * a.ldb * 2), kBufWord3);
-    // ao has room for the tallest tile (an array bound that depends on MT,
-    // captured by the lambdas below, makes the host pass drop the kernel).
-    uint32_t ao[4], bo[4];
+// Epilogue of a wavefront that holds a (32 RB) x (32 CB) block of C with its
+// first element at (m, n).  The MFMA operands are exchanged (B's fragment
+// first), so lane l holds row l % 32 of each 32 x 32 block and, in v =
+// 4 q .. 4 q + 3, the four consecutive columns 8 q + 4 (l / 32): they are
+// rounded to bf16 (v_cvt_pk_bf16_f32, nearest even), put into the
+// wavefront's own LDS rows (64 CB bytes, 16-byte chunks swizzled by row) and
+// read back as 16-byte pieces of rows, which leave as full cache lines.
+// Rounding in integer code and storing each value by itself took 4100
+// instructions a wavefront and 15 us of a 115 us 4096^3 product.
+// With COS the same pieces give the row sums P.C, P.P and C.C over the
+// block's columns (the values as stored), left in red[row][3].
+template <int RB, int CB, bool COS>
+__device__ __forceinline__ void finish_block(const GemmArgs& a, const f32x16 (&acc)[RB][CB], lds_t* own, int m,
+                                             int n, lds_f32* red)
+{
+    constexpr int kChunks = 4 * CB, kRowsStep = kWave / kChunks, kSteps = 32 * RB / kRowsStep;
+    constexpr int kRowB = 64 * CB;
+    const int lane = threadIdx.x & 63, l31 = lane & 31, half = lane >> 5;
+    const int c = lane % kChunks, r0 = lane / kChunks;
+    [[maybe_unused]] u32x4 p[COS ? kSteps : 1];
+    if constexpr (COS) {
+        const uint16_t* P = reinterpret_cast<const uint16_t*>(a.P) + n + c * 8;
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-        const int row = (w * MT + i) * 8 + (lane >> 3);
-        const int c = (lane & 7) ^ ((row >> 1) & 7);
-        if constexpr (GATHER) {
-            const int m = m0 + row;
-            int32_t r = m < a.M ? a.arows[m] : -1;
-            ao[i] = (r >= 0 && r < a.arow_count) ? (uint32_t)((int64_t)r * a.lda * 2 + c * 16) : kBadRow;
-        } else {
-            ao[i] = (uint32_t)(row * a.lda * 2 + c * 16);
+        for (int g = 0; g < kSteps; ++g) {
+            const int row = m + g * kRowsStep + r0;
+            p[g] = row < a.M ? *reinterpret_cast<const u32x4_any*>(P + (int64_t)row * a.ldp) : u32x4{0u, 0u, 0u, 0u};
         }
     }
+    auto at = [&](int r, int ch) { return own + r * kRowB + ((ch ^ ((CB == 2 ? r >> 1 : r >> 2) & (kChunks - 1))) * 16); };
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = (w * 4 + i) * 8 + (lane >> 3);
-        const int c = (lane & 7) ^ ((row >> 1) & 7);
-        bo[i] = (uint32_t)(row * a.ldb * 2 + c * 16);
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 x = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                *(lds_quad*)(at(i * 32 + l31, j * 4 + q) + half * 8) = __builtin_convertvector(x, bf16x4);
+            }
+    uint16_t* C = reinterpret_cast<uint16_t*>(a.C) + n + c * 8;
+#pragma unroll
+    for (int g = 0; g < kSteps; ++g) {
+        const int r = g * kRowsStep + r0;
+        const u32x4 v = *(const lds_chunk*)at(r, c);
+        if (m + r < a.M) *reinterpret_cast<u32x4_any*>(C + (int64_t)(m + r) * a.ldc) = v;
+        if constexpr (COS) {
+            static_assert(!COS || kChunks == 8, "a row's sums are over eight lanes");
+            float d = 0.f, pp = 0.f, cc = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                d = dot2(p[g][k], v[k], d);
+                pp = dot2(p[g][k], p[g][k], pp);
+                cc = dot2(v[k], v[k], cc);
+            }
+            d = sum8(d);
+            pp = sum8(pp);
+            cc = sum8(cc);
+            if (c == 0) {
+                red[r * 3] = d;
+                red[r * 3 + 1] = pp;
+                red[r * 3 + 2] = cc;
+            }
+        }
     }
-    const int dsta = w * MT * 1024, dstb = w * 4 * 1024;
-    auto issue = [&](lds_t* sa, lds_t* sb, int k0) {
+}
+
+// The tile's partial sums from those of its WN column blocks, in their order.
+template <int ROWS, int WN, int THREADS>
+__device__ __forceinline__ void finish_sums(const GemmArgs& a, const lds_f32* red, int m0, int tn)
+{
+    for (int r = threadIdx.x; r < ROWS; r += THREADS) {
+        if (m0 + r >= a.M) continue;
+        float s[3] = {0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void*)(sa + dsta + i * 1024), 16, ao[i], k0 * 2, 0, 0);
+        for (int q = 0; q < WN; ++q)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + dstb + i * 1024), 16, bo[i], k0 * 2, 0, 0);
+            for (int k = 0; k < 3; ++k) s[k] += red[(q * ROWS + r) * 3 + k];
+        float* out = a.part + ((int64_t)(m0 + r) * a.part_cols + tn) * 3;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) out[k] = s[k];
+    }
+}
+
+// ---- large tiles: (64 MT) x 256, eight wavefronts in two alternating groups --
+//
+// Wavefront (wm, wn) of the 2 x 4 grid owns (32 MT) x 64 of C; the two
+// wavefronts of a SIMD are of different wm.  A k-tile (64 of K) lies in LDS
+// as four parts, each read whole in one phase: A0 (the wavefronts' first 64
+// rows), A1 (the rest), B0 and B1 (their first and second 32 columns); two
+// k-tiles are held.  Each phase of a wavefront is a memory part (LDS reads of
+// the fragments it needs next, LDS-destination loads into the part that the
+// phase before has freed) and an MFMA part (8 MFMAs, 256 cycles), separated
+// by barriers; the wm = 1 wavefronts run one barrier behind, so each SIMD's
+// matrix pipe always has one wavefront in its MFMA part while the other
+// reads (without the offset: 106 -> 123 us at 4096^3).  A part is refilled as
+// soon as it is free, so its loads have nearly two k-tiles to arrive and no
+// wait ever drains the queue.
+//
+// Bound by power and LDS together: at 4096^3 the MFMAs alone take 65 us, with
+// the LDS reads 92 us at the clock that the chip then holds, and 105 us with
+// the loads (a two-stage loop that waits for all loads before each k-tile:
+// 114 us; the library's kernel: 90 us).  Barrier counts are equal in every
+// wavefront: each runs the same phases and one extra barrier (wm = 1 before,
+// wm = 0 after).
+constexpr int kPBN = 256, kPThreads = 512, kPBuf = 4 * kSlot;
+constexpr int kOffA1 = kSlot, kOffB0 = 2 * kSlot, kOffB1 = 3 * kSlot;
+
+template <int MT, bool GATHER, bool COS>
+__global__ __launch_bounds__(kPThreads, 1) void gemm_large_kernel(GemmArgs a)
+{
+    static_assert(MT >= 2 && MT <= 4, "A1 holds MT - 2 blocks of 32 rows per wavefront");
+    constexpr int BM = 64 * MT;
+    constexpr int kA1 = MT - 2;          // LDS-destination loads of A1 per wavefront (A0, B0, B1: 2 each)
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * kPBuf];
+    __shared__ float red_[COS ? 4 * BM * 3 : 1];
+    lds_t* const sm = (lds_t*)smem;
+    const uint32_t sbase = (uint32_t)(uintptr_t)sm;
+
+    int tm, tn;
+    if (!tile_of((a.M + BM - 1) / BM, (a.N + kPBN - 1) / kPBN, tm, tn)) return;   // whole workgroup
+    const int m0 = tm * BM, n0 = tn * kPBN;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = w >> 2, wn = w & 3;
+
+    // ---- global -> LDS.  Rows of 128 bytes; lane l of wavefront w fills
+    // physical chunk l % 8 of row 64 j + 8 w + l / 8 of a part, which holds
+    // logical chunk (l % 8) ^ ((row / 2) % 8).  Rows past A or B, and gathered
+    // rows out of range, lie past the resource and read as zeros.
+    const uint16_t* A = reinterpret_cast<const uint16_t*>(a.A);
+    const uint16_t* B = reinterpret_cast<const uint16_t*>(a.B);
+    const u32x4 ra = GATHER ? buffer_of(A, a.arow_count * a.lda * 2)
+                            : buffer_of(A + (int64_t)m0 * a.lda, (int64_t)(a.M - m0) * a.lda * 2);
+    const u32x4 rb = buffer_of(B + (int64_t)n0 * a.ldb, (int64_t)(a.N - n0) * a.ldb * 2);
+    uint32_t oa0[2], oa1[2], ob[2][2];
+    {
+        const int row = w * 8 + (lane >> 3);
+        const uint32_t c = (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
+        auto a_off = [&](int r) -> uint32_t {   // r: row of the tile
+            if constexpr (GATHER) {
+                const int g = m0 + r < a.M ? a.arows[m0 + r] : -1;
+                return (g >= 0 && g < a.arow_count) ? (uint32_t)((int64_t)g * a.lda * 2) + c : kBadRow;
+            } else {
+                return (uint32_t)(r * a.lda * 2) + c;
+            }
+        };
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            oa0[j] = a_off(j * 32 * MT + row);
+            if constexpr (MT == 4) oa1[j] = a_off(j * 32 * MT + 64 + row);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                ob[h][j] = (uint32_t)(((2 * j + (row >> 5)) * 64 + h * 32 + (row & 31)) * a.ldb * 2) + c;
+        }
+        if constexpr (MT == 3) oa1[0] = a_off((row >> 5) * 96 + 64 + (row & 31));
+    }
+    const uint32_t dst = sbase + (uint32_t)w * 1024;
+    auto buf_of = [](int kt) { return (uint32_t)(kt & 1) * kPBuf; };
+    auto load_a0 = [&](int kt) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) load_lds(ra, dst + buf_of(kt) + j * 8192, oa0[j], (uint32_t)kt * 128);
+    };
+    auto load_a1 = [&](int kt) {
+#pragma unroll
+        for (int j = 0; j < kA1; ++j) load_lds(ra, dst + buf_of(kt) + kOffA1 + j * 8192, oa1[j], (uint32_t)kt * 128);
+    };
+    auto load_b = [&](int h, int kt) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            load_lds(rb, dst + buf_of(kt) + (h ? kOffB1 : kOffB0) + j * 8192, ob[h][j], (uint32_t)kt * 128);
     };
 
     // ---- fragment reads: lane l reads row l % 32 of a 32-row block, logical
-    // chunk 2 kk + l / 32, which sits at physical chunk (2 kk + l / 32) ^ sw.
+    // chunk 2 kk + l / 32
     const int l31 = lane & 31, half = lane >> 5;
-    const int sw = (l31 >> 1) & 7, shi = sw >> 1, slo = sw & 1;
-    int offA[4], offB[4];
+    uint32_t fa[4], fb[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-        const int cb = 32 * (kk ^ shi) + 16 * (half ^ slo);
-        offA[kk] = (wm * 32 * MT + l31) * 128 + cb;
-        offB[kk] = (wn * 64 + l31) * 128 + cb;
+        const uint32_t cb = (uint32_t)(((2 * kk + half) ^ ((l31 >> 1) & 7)) * 16);
+        fa[kk] = (uint32_t)l31 * 128 + cb;
+        fb[kk] = (uint32_t)(wn * 32 + l31) * 128 + cb;
     }
-
     f32x16 acc[MT][2];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -335,169 +495,141 @@ __global__ __launch_bounds__(kWThreads, 1) void gemm_wide_kernel(GemmArgs a)
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    // One k-tile: the fragments of step kk+1 are read before the MFMAs of step
-    // kk (the scheduling barriers keep that order).
-    auto compute = [&](const lds_t* sa, const lds_t* sb) {
-        bf16x8 fa[2][MT], fb[2][2];
+    // Fragments of A0, of A1 (in A0's place when the phases allow it) and of
+    // both column blocks.
+    bf16x8 fA[MT == 3 ? 3 : 2][4], fB[2][4];
+    auto read_a0 = [&](int kt) {
+        const lds_t* p = sm + (buf_of(kt) + (uint32_t)wm * 8192);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) fa[0][i] = *(const lds_frag*)(sa + offA[0] + i * 4096);
+        for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) fb[0][j] = *(const lds_frag*)(sb + offB[0] + j * 4096);
+            for (int i = 0; i < 2; ++i) fA[i][kk] = *(const lds_frag*)(p + fa[kk] + i * 4096);
+    };
+    auto read_a1 = [&](int kt) {
+        const lds_t* p = sm + (buf_of(kt) + kOffA1 + (uint32_t)(wm * 4096 * kA1));
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const int cur = kk & 1, nxt = cur ^ 1;
-            if (kk < 3) {
+        for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-                for (int i = 0; i < MT; ++i) fa[nxt][i] = *(const lds_frag*)(sa + offA[kk + 1] + i * 4096);
+            for (int i = 0; i < kA1; ++i) fA[MT == 3 ? 2 : i][kk] = *(const lds_frag*)(p + fa[kk] + i * 4096);
+    };
+    auto read_b = [&](int h, int kt) {
+        const lds_t* p = sm + (buf_of(kt) + (h ? kOffB1 : kOffB0));
 #pragma unroll
-                for (int j = 0; j < 2; ++j) fb[nxt][j] = *(const lds_frag*)(sb + offB[kk + 1] + j * 4096);
-            }
-            __builtin_amdgcn_sched_barrier(0);
+        for (int kk = 0; kk < 4; ++kk) fB[h][kk] = *(const lds_frag*)(p + fb[kk]);
+    };
+    // Blocks i0 .. i0 + n - 1 of the wavefront's rows (fragments from f0 on)
+    // times column blocks j0 .. j1, between barriers.
+    auto mma = [&](int i0, int n, int f0, int j0, int j1) {
+        wait_reads();
+        barrier();
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-            for (int i = 0; i < MT; ++i)
+        for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+            for (int i = 0; i < n; ++i)
+#pragma unroll
+                for (int j = j0; j <= j1; ++j)
+                    acc[i0 + i][j] =
+                        __builtin_amdgcn_mfma_f32_32x32x16_bf16(fB[j][kk], fA[f0 + i][kk], acc[i0 + i][j], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+        barrier();
     };
 
-    // Two stages.  Before each k-tile every wavefront waits for its own
-    // LDS-destination loads, then the barrier makes all of them visible and
-    // guarantees the other stage is no longer read: the next k-tile's loads go
-    // there while this one is computed.
-    // The host sends only an even number of k-tiles (K % 128 == 0) here: a
-    // loop with a single exit keeps the accumulators in place.
-    //
-    // Cosine epilogue: the tile's [64 MT, 256] block of P (at most 128 KB) is
-    // staged through the two freed stages.  Rows 0-127 (all those of
-    // wavefronts 0-3) go into stage 0 during the last k-tile; rows 128 and up
-    // into stage 1 while wavefronts 0-3 form their sums.  Stage h holds row
-    // 64 g + r of its 128 rows at array g (A or B part of the stage), byte
-    // r * 512.
+    // One k-tile.  Tail 0: kt + 2 exists; 1: kt is the last but one; 2: the
+    // last.  Each wait leaves in flight exactly the loads issued after those
+    // that the next phase reads; the barriers in between publish them.
     const int KT = a.K / kBK;
-    [[maybe_unused]] __amdgpu_buffer_rsrc_t rp;
-    if constexpr (COS) {
-        const int64_t p_bytes = (int64_t)(a.M - m0) * a.ldp * 2;
-        rp = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)(reinterpret_cast<const uint16_t*>(a.P) + (int64_t)m0 * a.ldp + n0), (short)0,
-            (int)(p_bytes < (int64_t)kBadRow ? p_bytes : (int64_t)kBadRow - 1), kBufWord3);
-    }
-    auto issue_p = [&](int h, lds_t* sa, lds_t* sb) {
-        lds_t* arr = w < 4 ? sa : sb;
-        const int rows = BMW - 128 * h < 128 ? BMW - 128 * h : 128;   // rows of P in this stage
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int q = (w & 3) * 8 + i;   // 1 KB block of the array: rows 2q, 2q+1
-            const int rh = (w >> 2) * 64 + 2 * q;   // first of the two rows within the stage
-            if (rh < rows)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rp, (lds_void*)(arr + q * 1024), 16,
-                    (uint32_t)((h * 128 + rh + (lane >> 5)) * a.ldp * 2 + (lane & 31) * 16), 0, 0, 0);
-        }
-    };
-
-    issue(a0, b0, 0);
-    for (int kt = 0; kt < KT; kt += 2) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        issue(a1, b1, (kt + 1) * kBK);
-        compute(a0, b0);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (kt + 2 < KT) {
-            issue(a0, b0, (kt + 2) * kBK);
+    auto step = [&](int kt, auto tail) {
+        constexpr int T = decltype(tail)::value;
+        constexpr bool more = T == 0, next = T < 2;
+        if constexpr (MT == 4) {
+            read_a0(kt);
+            if constexpr (more) load_b(0, kt + 2);
+            wait_loads<more ? 12 : next ? 10 : 2>();   // B1
+            mma(0, 2, 0, 0, 0);
+            read_b(1, kt);
+            if constexpr (more) load_a0(kt + 2);
+            wait_loads<more ? 12 : next ? 8 : 0>();    // A1
+            mma(0, 2, 0, 1, 1);
+            read_a1(kt);
+            if constexpr (more) load_b(1, kt + 2);
+            if constexpr (next) wait_loads<more ? 12 : 6>();   // B0 of kt + 1
+            mma(2, 2, 0, 0, 0);
+            if constexpr (next) read_b(0, kt + 1);
+            if constexpr (more) load_a1(kt + 2);
+            if constexpr (next) wait_loads<more ? 12 : 4>();   // A0 of kt + 1
+            mma(2, 2, 0, 1, 1);
+        } else if constexpr (MT == 3) {
+            read_a0(kt);
+            if constexpr (more) load_b(0, kt + 2);
+            wait_loads<more ? 9 : next ? 7 : 0>();     // A1, B1
+            mma(0, 2, 0, 0, 0);
+            read_a1(kt);
+            read_b(1, kt);
+            if constexpr (more) load_a0(kt + 2);
+            if constexpr (next) wait_loads<more ? 9 : 5>();    // B0 of kt + 1
+            mma(2, 1, 2, 0, 1);
+            if constexpr (next) read_b(0, kt + 1);
+            if constexpr (more) {
+                load_a1(kt + 2);
+                load_b(1, kt + 2);
+            }
+            if constexpr (next) wait_loads<more ? 10 : 3>();   // A0 of kt + 1
+            mma(0, 2, 0, 1, 1);
         } else {
-            if constexpr (COS) issue_p(0, a0, b0);
+            read_a0(kt);
+            if constexpr (next) load_b(1, kt + 1);
+            if constexpr (more) load_b(0, kt + 2);
+            wait_loads<more ? 6 : next ? 4 : 0>();     // B1, B0 of kt + 1
+            mma(0, 2, 0, 0, 0);
+            read_b(1, kt);
+            if constexpr (next) read_b(0, kt + 1);
+            if constexpr (more) load_a0(kt + 2);
+            if constexpr (next) wait_loads<more ? 6 : 2>();    // A0 of kt + 1
+            mma(0, 2, 0, 1, 1);
         }
-        compute(a1, b1);
-    }
-
-    // ---- epilogue ----------------------------------------------------------
-    // The row stride passes through an empty asm so that no output address is
-    // formed before the main loop (64 row offsets held across it would spill).
-    int64_t ldc = a.ldc;
-    asm volatile("" : "+s"(ldc));
-    uint16_t* C = reinterpret_cast<uint16_t*>(a.C);
-    auto store_c = [&]() {
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = m0 + wm * 32 * MT + i * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
-                if (m < a.M) {
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        C[(int64_t)m * ldc + n0 + wn * 64 + j * 32 + l31] = to_bf16(acc[i][j][v]);
-                }
-            }
-    };
-    // Per-row sums P.C, P.P and C.C over this wavefront's 64 columns, from P
-    // staged in LDS; rows past M have P = 0 and C = 0 (their A rows read as
-    // zeros) and are never used.
-    auto cos_part = [&]() {
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r0 = wm * 32 * MT + i * 32;   // first row of this 32-row block (uniform)
-                const int rr = (r0 & 127) + (v >> 2) * 8 + half * 4 + (v & 3);   // row within its stage
-                const lds_t* arr = r0 >= 128 ? ((r0 & 127) >= 64 ? b1 : a1) : ((r0 & 127) >= 64 ? b0 : a0);
-                float dot = 0.f, pp = 0.f, cc = 0.f;
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int col = wn * 64 + j * 32 + l31;
-                    const float pv = bf16_lo(*(const __attribute__((address_space(3))) uint16_t*)(
-                        arr + (rr & 63) * 512 + col * 2));
-                    const float c = bf16_lo(to_bf16(acc[i][j][v]));   // the value stored
-                    dot = fmaf(pv, c, dot);
-                    pp = fmaf(pv, pv, pp);
-                    cc = fmaf(c, c, cc);
-                }
-                dot = half_sum(dot);
-                pp = half_sum(pp);
-                cc = half_sum(cc);
-                if (l31 == 31) {
-                    float* r = red + ((size_t)wn * kBM + r0 + (v >> 2) * 8 + half * 4 + (v & 3)) * 3;
-                    r[0] = dot;
-                    r[1] = pp;
-                    r[2] = cc;
-                }
-            }
     };
 
-    if constexpr (!COS) {
-        store_c();
+    // The first two k-tiles, in the order in which the steps count them (MT =
+    // 2 holds B1 for one phase less and loads it one k-tile ahead).
+    load_b(0, 0);
+    load_a0(0);
+    load_b(1, 0);
+    load_a1(0);
+    if (KT > 1) {
+        load_b(0, 1);
+        load_a0(1);
+        if constexpr (MT > 2) {
+            load_b(1, 1);
+            load_a1(1);
+        }
+        wait_loads<MT == 4 ? 12 : MT == 3 ? 10 : 6>();   // B0, A0 of the first
     } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();   // P rows 0-127 in stage 0; stage 1 no longer read
-        issue_p(1, a1, b1);
-        if (wm == 0) cos_part();
-        store_c();
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();   // P rows 128 and up in stage 1
-        if (wm == 1) cos_part();
-        __syncthreads();
-        // one thread per tile row: the four N-quarters in order, then this
-        // tile's partials
-        if (tid < BMW) {
-            const int m = m0 + tid;
-            if (m < a.M) {
-                float d = 0.f, p = 0.f, q = 0.f;
-#pragma unroll
-                for (int qn = 0; qn < 4; ++qn) {
-                    const float* r = red + ((size_t)qn * kBM + tid) * 3;
-                    d += r[0];
-                    p += r[1];
-                    q += r[2];
-                }
-                float* out = a.part + ((int64_t)m * a.part_cols + n0 / kWBN) * 3;
-                out[0] = d;
-                out[1] = p;
-                out[2] = q;
-            }
-        }
+        wait_loads<MT == 4 ? 4 : MT == 3 ? 3 : 2>();
+    }
+    barrier();
+    read_b(0, 0);
+    wait_reads();   // the first step refills B0
+    barrier();
+    if (wm == 1) barrier();
+    int kt = 0;
+    for (; kt + 2 < KT; ++kt) step(kt, std::integral_constant<int, 0>{});
+    if (KT > 1) step(kt++, std::integral_constant<int, 1>{});
+    step(kt, std::integral_constant<int, 2>{});
+    if (wm == 0) barrier();
+
+    // Every wavefront has read its last fragments: the buffers are free.
+    lds_t* own = sm + w * (32 * MT * 128);
+    lds_f32* red = (lds_f32*)red_;
+    const int n = n0 + wn * 64;
+    if (n < a.N)   // N is a multiple of 128: whole wavefronts lie past it
+        finish_block<MT, 2, COS>(a, acc, own, m0 + wm * 32 * MT, n, red + (wn * BM + wm * 32 * MT) * 3);
+    if constexpr (COS) {
+        if (n >= a.N)
+            for (int r = lane; r < 32 * MT * 3; r += kWave) red[(wn * BM + wm * 32 * MT) * 3 + r] = 0.f;
+        wait_reads();
+        barrier();
+        finish_sums<BM, 4, kPThreads>(a, red, m0, tn);
     }
 }
 
@@ -519,32 +651,32 @@ __global__ __launch_bounds__(256) void cos_finish_kernel(const float* part, int 
     s[m] = v;
 }
 
-// The wide kernel takes the shape when N is a multiple of 256, K of 128 (an
-// even number of k-tiles) and every buffer offset it forms fits 31 bits.
-bool use_wide(const GemmArgs& a)
+// The large kernel takes every shape whose buffer offsets (rows of a tile, or
+// all of A's rows when they are gathered) fit 31 bits: at N % 256 = 128 and K %
+// 128 = 64 too it is the faster one (3001 x 1664 x 4160: 45 against 93 us).
+bool use_large(const GemmArgs& a)
 {
-    if (a.N % kWBN || a.K % (2 * kBK)) return false;
     const int64_t lim = (int64_t)kBadRow;
-    if ((int64_t)kBM * a.lda * 2 >= lim || (int64_t)kWBN * a.ldb * 2 >= lim) return false;
-    if (a.arows && a.arow_count * a.lda * 2 >= lim) return false;
-    if (a.P && (int64_t)kBM * a.ldp * 2 >= lim) return false;
-    return true;
+    if ((int64_t)kBM * a.lda * 2 >= lim || (int64_t)kPBN * a.ldb * 2 >= lim) return false;
+    return !a.arows || a.arow_count * a.lda * 2 < lim;
 }
 
 int g_cus = 256;         // compute units of the device (set by gemm_prepare)
 int g_force_mt = 0;      // tile height override: 0 = model, else 2, 3 or 4
 
-// Tile height of the wide kernel (MFMA tiles per wavefront along M): the one
+// Tile height of the large kernel (MFMA tiles per wavefront along M): the one
 // with the least modelled time, (tile waves over the CUs) x (rows per tile),
-// where shorter tiles pay for their higher LDS traffic per MFMA.
-int wide_mt(int M, int N)
+// where shorter tiles pay for their higher LDS traffic per MFMA.  Rates on
+// shapes that fill the CUs, as 256 : 192 : 128 rows: 1340 : 1225 : 1180
+// TFLOP/s (4096^3 and 36864 x 1024 x 4096), so 9 % and 14 % more per row.
+int large_mt(int M, int N)
 {
     if (g_force_mt) return g_force_mt;
-    const double cost_per_row[5] = {0, 0, 1.2, 1.05, 1.0};
+    const double cost_per_row[5] = {0, 0, 1.14, 1.09, 1.0};
     int best = 4;
     double best_t = 0;
     for (int mtw = 4; mtw >= 2; --mtw) {
-        const int64_t tiles = (int64_t)((M + 64 * mtw - 1) / (64 * mtw)) * (N / kWBN);
+        const int64_t tiles = (int64_t)((M + 64 * mtw - 1) / (64 * mtw)) * ((N + kPBN - 1) / kPBN);
         const int64_t waves = (tiles + g_cus - 1) / g_cus;
         const double t = (double)waves * mtw * cost_per_row[mtw];
         if (mtw == 4 || t < best_t) {
@@ -555,30 +687,30 @@ int wide_mt(int M, int N)
     return best;
 }
 
-void launch_wide(const GemmArgs& a, int mtw, bool gather, bool cos, int grid, hipStream_t s)
+void launch_large(const GemmArgs& a, int mtw, bool gather, bool cos, int grid, hipStream_t s)
 {
-    const dim3 g(grid), b(kWThreads);
+    const dim3 g(grid), b(kPThreads);
     if (mtw == 4) {
         if (gather)
-            hipLaunchKernelGGL((gemm_wide_kernel<4, true, false>), g, b, 0, s, a);
+            hipLaunchKernelGGL((gemm_large_kernel<4, true, false>), g, b, 0, s, a);
         else if (cos)
-            hipLaunchKernelGGL((gemm_wide_kernel<4, false, true>), g, b, 0, s, a);
+            hipLaunchKernelGGL((gemm_large_kernel<4, false, true>), g, b, 0, s, a);
         else
-            hipLaunchKernelGGL((gemm_wide_kernel<4, false, false>), g, b, 0, s, a);
+            hipLaunchKernelGGL((gemm_large_kernel<4, false, false>), g, b, 0, s, a);
     } else if (mtw == 3) {
         if (gather)
-            hipLaunchKernelGGL((gemm_wide_kernel<3, true, false>), g, b, 0, s, a);
+            hipLaunchKernelGGL((gemm_large_kernel<3, true, false>), g, b, 0, s, a);
         else if (cos)
-            hipLaunchKernelGGL((gemm_wide_kernel<3, false, true>), g, b, 0, s, a);
+            hipLaunchKernelGGL((gemm_large_kernel<3, false, true>), g, b, 0, s, a);
         else
-            hipLaunchKernelGGL((gemm_wide_kernel<3, false, false>), g, b, 0, s, a);
+            hipLaunchKernelGGL((gemm_large_kernel<3, false, false>), g, b, 0, s, a);
     } else {
         if (gather)
-            hipLaunchKernelGGL((gemm_wide_kernel<2, true, false>), g, b, 0, s, a);
+            hipLaunchKernelGGL((gemm_large_kernel<2, true, false>), g, b, 0, s, a);
         else if (cos)
-            hipLaunchKernelGGL((gemm_wide_kernel<2, false, true>), g, b, 0, s, a);
+            hipLaunchKernelGGL((gemm_large_kernel<2, false, true>), g, b, 0, s, a);
         else
-            hipLaunchKernelGGL((gemm_wide_kernel<2, false, false>), g, b, 0, s, a);
+            hipLaunchKernelGGL((gemm_large_kernel<2, false, false>), g, b, 0, s, a);
     }
 }
 
@@ -601,7 +733,7 @@ hipError_t gemm_prepare()
     int dev = 0;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&g_cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-    // TR_GEMM_TILE_ROWS = 128, 192 or 256 pins the wide kernel's tile height
+    // TR_GEMM_TILE_ROWS = 128, 192 or 256 pins the large kernel's tile height
     // (tuning and tests); anything else leaves the choice to the model.
     const char* env = getenv("TR_GEMM_TILE_ROWS");
     const int rows = env ? atoi(env) : 0;
@@ -620,13 +752,13 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     if (a.M == 0) return hipSuccess;
     const bool gather = a.arows != nullptr, cos = a.P != nullptr;
     if (gather && cos) return hipErrorInvalidValue;
-    const bool wide = use_wide(a);
-    const int mtw = wide ? wide_mt(a.M, a.N) : 4;
-    const int bm = wide ? 64 * mtw : kBM, bn = wide ? kWBN : kBN;
-    const int tiles = ((a.M + bm - 1) / bm) * (a.N / bn);
+    const bool large = use_large(a);
+    const int mtw = large ? large_mt(a.M, a.N) : 4;
+    const int bm = large ? 64 * mtw : kBM, bn = large ? kPBN : kBN;
+    const int tiles = ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn);
     const int grid = ((tiles + kXcds - 1) / kXcds) * kXcds;
-    if (wide) {
-        launch_wide(a, mtw, gather, cos, grid, s);
+    if (large) {
+        launch_large(a, mtw, gather, cos, grid, s);
     } else {
         const size_t lds = kLdsA + kLdsB + (cos ? kLdsRed : 0);
         if (gather)
@@ -638,7 +770,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !cos) return e;
-    hipLaunchKernelGGL(cos_finish_kernel, dim3((a.M + 255) / 256), dim3(256), 0, s, a.part, a.part_cols, a.N / bn,
+    hipLaunchKernelGGL(cos_finish_kernel, dim3((a.M + 255) / 256), dim3(256), 0, s, a.part, a.part_cols, (a.N + bn - 1) / bn,
                        a.M, a.s_out);
     return hipGetLastError();
 }

@@ -55,8 +55,7 @@ def check_gemm(C, A_rows, B):
     assert not bad.any(), "%d outputs outside the bound, first at %s" % (bad.sum(), np.argwhere(bad)[:3])
 
 
-# N % 256 == 0 with K % 128 == 0 runs the wide tiling (256 x 256, LDS-destination
-# loads), every other shape the narrow one (256 x 128, register prefetch).
+# Whole and half column tiles (N % 256), odd and even numbers of k-tiles (K / 64).
 @pytest.mark.parametrize("M,N,K,pad", [(1, 128, 64, 0), (300, 256, 128, 0), (257, 384, 512, 8),
                                        (130, 256, 192, 0), (257, 512, 512, 8), (1000, 1024, 4096, 0),
                                        (4096, 4096, 4096, 0)])
@@ -93,10 +92,10 @@ def test_gemm_gathered_rows(N):
 
 @pytest.mark.parametrize("tile_rows", [None, 128, 192, 256])
 def test_gemm_tilings_agree_bit_for_bit(tile_rows, monkeypatch):
-    """The wide (N % 256 == 0) and narrow (N % 256 == 128) tilings run the same
-    MFMA sequence for every output element, so the columns they share are
-    bit-identical, plain and gathered, at every tile height of the wide one
-    (TR_GEMM_TILE_ROWS pins it; None leaves it to the model)."""
+    """Products with N % 256 == 0 and N % 256 == 128 run the same MFMA sequence
+    for every output element, so the columns they share are bit-identical,
+    plain and gathered, at every tile height (TR_GEMM_TILE_ROWS pins it; None
+    leaves it to the model)."""
     if tile_rows is not None:
         monkeypatch.setenv("TR_GEMM_TILE_ROWS", str(tile_rows))
     say("gemm wide vs narrow 1000 x 512/384 x 1024, tile rows", tile_rows)
