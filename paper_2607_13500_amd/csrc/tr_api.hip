@@ -183,7 +183,6 @@ struct FusedCopy {
     const void* X = nullptr;
     void* out = nullptr;
     int64_t row_bytes = 0;
-    bool vec = false;
     int elem = 4;
 };
 
@@ -211,7 +210,6 @@ hipError_t run_select(const tr_ctx* c, const Plan& pl, const float* key_imp, con
         a.gX = fc.X;
         a.gout = fc.out;
         a.grow_bytes = fc.row_bytes;
-        a.gvec = fc.vec ? 1 : 0;
         a.gelem = fc.elem;
         a.ggroups = tr::select_small_groups(B, kmin, c->cus);
     }
@@ -450,10 +448,6 @@ tr_status reduce_impl(tr_ctx* c, ReduceCall r)
     if (need_x && (c->p.flags & TR_FLAG_SHANNON)) mode |= tr::kScoreShannon;
 
     const int64_t row_bytes = (int64_t)c->p.D * c->eb;
-    const int64_t rowc_bytes = (int64_t)c->Dc * c->eb;
-    const bool vec_score = aligned16(r.X) && aligned16(r.X_pre) && aligned16(r.X_post) &&
-                           row_bytes % 16 == 0 && rowc_bytes % 16 == 0;
-    const bool vec_gather = aligned16(r.X) && aligned16(r.out) && row_bytes % 16 == 0;
     tr::GemmArgs ga{};
     if (r.W) {
         if (c->p.dtype != TR_BF16) return fail(TR_EUNSUPPORTED, "the projection needs a bf16 context");
@@ -500,7 +494,7 @@ tr_status reduce_impl(tr_ctx* c, ReduceCall r)
         sa.out_s = r.out_s;
         sa.logD = (float)log((double)c->p.D);
         sa.nonfinite = c->nonfinite;
-        if ((e = tr::launch_score(sa, c->p.dtype == TR_BF16, vec_score, mode, s)) != hipSuccess)
+        if ((e = tr::launch_score(sa, c->p.dtype == TR_BF16, mode, s)) != hipSuccess)
             return hip_fail(e, "score kernel launch");
     }
     if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -515,7 +509,6 @@ tr_status reduce_impl(tr_ctx* c, ReduceCall r)
         fc.X = r.X;
         fc.out = r.out;
         fc.row_bytes = row_bytes;
-        fc.vec = vec_gather;
         fc.elem = c->eb;
     }
     if ((e = run_select(c, pl, c->key_imp, r.key_s ? r.key_s : c->key_s, r.out_idx, r.out_src,
@@ -524,7 +517,7 @@ tr_status reduce_impl(tr_ctx* c, ReduceCall r)
     if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
 
     if (r.W) e = tr::launch_gemm(ga, s);
-    else if (!fc.X) e = tr::launch_gather(r.X, r.out, c->rows, pl.sum_k, pl.sum_n, row_bytes, c->eb, vec_gather, s);
+    else if (!fc.X) e = tr::launch_gather(r.X, r.out, c->rows, pl.sum_k, pl.sum_n, row_bytes, c->eb, s);
     if (e != hipSuccess) return hip_fail(e, r.W ? "projection kernel launch" : "gather kernel launch");
     if (ev && (e = hipEventRecord(ev[3], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     if (ev) ++c->timed;
@@ -731,10 +724,6 @@ tr_status tr_score(tr_ctx* c, const void* X, const void* X_pre, const void* X_po
         return fail(TR_EUNSUPPORTED, "X, X_pre and X_post must be aligned to the element size (%d bytes)", c->eb);
     if (((uintptr_t)key_imp | (uintptr_t)key_s | (uintptr_t)out_h2) & 3u)
         return fail(TR_EUNSUPPORTED, "score outputs must be 4-byte aligned");
-    const int64_t row_bytes = (int64_t)c->p.D * c->eb;
-    const int64_t rowc_bytes = (int64_t)c->Dc * c->eb;
-    const bool vec = aligned16(X) && aligned16(X_pre) && aligned16(X_post) && row_bytes % 16 == 0 &&
-                     rowc_bytes % 16 == 0;
     DeviceGuard g(c->device);
     if (!g.ok) return fail(TR_EDEVICE, "hipSetDevice(%d) failed", c->device);
     tr::ScoreArgs sa;
@@ -752,7 +741,7 @@ tr_status tr_score(tr_ctx* c, const void* X, const void* X_pre, const void* X_po
     sa.nonfinite = c->nonfinite;
     int mode = (want_x ? tr::kScoreImp : 0) | (want_c ? tr::kScoreSim : 0);
     if (want_x && (c->p.flags & TR_FLAG_SHANNON)) mode |= tr::kScoreShannon;
-    hipError_t e = tr::launch_score(sa, c->p.dtype == TR_BF16, vec, mode, static_cast<hipStream_t>(stream));
+    hipError_t e = tr::launch_score(sa, c->p.dtype == TR_BF16, mode, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "score kernel launch");
     return TR_OK;
 }

@@ -32,8 +32,7 @@ struct SelectArgs {
     const void* gX;         // [sum N] rows of grow_bytes, or nullptr: no fused gather
     void* gout;             // [sum K] rows of grow_bytes
     int64_t grow_bytes;
-    int32_t gvec;           // 1: 16-byte copies (bases and row pitch 16-byte aligned)
-    int32_t gelem;          // element bytes (2 or 4) of the element-wise copy
+    int32_t gelem;          // element bytes (2 or 4)
     int32_t ggroups;        // workgroups per image of the small-image selection (>= 1)
     ImageDesc desc[kMaxDescPerLaunch];
 };
@@ -65,7 +64,7 @@ hipError_t launch_select(const SelectArgs& a, int nmax, hipStream_t s);
 // ---- gather of kept rows ---------------------------------------------------
 // rows[r] outside [0, nrows) are skipped (their output row is left as is).
 hipError_t launch_gather(const void* X, void* out, const int32_t* rows, int64_t nout, int64_t nrows,
-                         int64_t row_bytes, int elem_bytes, bool vec, hipStream_t s);
+                         int64_t row_bytes, int elem_bytes, hipStream_t s);
 
 // ---- measurement: streaming-read ceiling --------------------------------------
 // Reads bytes / 16 chunks of p (16-byte aligned) once; at most sink_words

@@ -33,9 +33,8 @@ constexpr int kScoreImp = 1;   // Eq. (3)-(4) from X: key_imp, out_h2
 constexpr int kScoreSim = 2;   // Eq. (6) from X_pre, X_post: key_s, out_s
 constexpr int kScoreShannon = 4;   // with kScoreImp: Shannon variant (key KL = log D - H1, out H1)
 
-// bf16: true for bfloat16 rows, false for fp32.  vec: every row start is
-// 16-byte aligned (vector loads); otherwise element loads with the same
-// per-lane arithmetic order.
-hipError_t launch_score(const ScoreArgs& a, bool bf16, bool vec, int mode, hipStream_t s);
+// bf16: true for bfloat16 rows, false for fp32.  Rows may start at any
+// element; a row's arithmetic does not depend on where it starts.
+hipError_t launch_score(const ScoreArgs& a, bool bf16, int mode, hipStream_t s);
 
 }  // namespace tr

@@ -94,43 +94,65 @@ __device__ __forceinline__ void unpack(const Raw& r, float* v)
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));   // 16 bytes at any element
 
-// Load full chunk c of a row.  Every byte is read exactly once, so the vector
-// path uses non-temporal loads (streamed past the caches: measured 7.0 vs
-// 6.2 TB/s for this access pattern on MI355X).
-template <bool BF16, bool VEC>
-__device__ __forceinline__ Raw load_chunk(const char* row, int c)
+// The 16 bytes at byte `off` of a row.  Every byte is read exactly once, so the
+// loads are non-temporal (streamed past the caches: measured 7.0 vs 6.2 TB/s
+// for this access pattern on MI355X).  A row may start at any element: the
+// 16-byte global load takes any byte address.
+__device__ __forceinline__ Raw load16(const char* row, uint32_t off)
 {
     Raw r;
-    if constexpr (VEC) {
-        const u32x4 q = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row + (size_t)c * 16));
-        r.w[0] = q.x;
-        r.w[1] = q.y;
-        r.w[2] = q.z;
-        r.w[3] = q.w;
-    } else if constexpr (BF16) {
-        const uint16_t* e = reinterpret_cast<const uint16_t*>(row) + (size_t)c * 8;
+    const u32x4 q = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(row + off));
+    r.w[0] = q.x;
+    r.w[1] = q.y;
+    r.w[2] = q.z;
+    r.w[3] = q.w;
+    return r;
+}
+
+// A whole row of m elements, fewer than a chunk holds, zero-padded.
+template <bool BF16>
+__device__ __forceinline__ Raw load_short(const char* row, int m)
+{
+    Raw r{{0u, 0u, 0u, 0u}};
+    if constexpr (BF16) {
+        const uint16_t* e = reinterpret_cast<const uint16_t*>(row);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) r.w[k] = (uint32_t)e[2 * k] | ((uint32_t)e[2 * k + 1] << 16);
+        for (int k = 0; k < 7; ++k)
+            if (k < m) r.w[k >> 1] |= (uint32_t)e[k] << (16 * (k & 1));
     } else {
-        const uint32_t* e = reinterpret_cast<const uint32_t*>(row) + (size_t)c * 4;
+        const uint32_t* e = reinterpret_cast<const uint32_t*>(row);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) r.w[k] = e[k];
+        for (int k = 0; k < 3; ++k)
+            if (k < m) r.w[k] = e[k];
     }
     return r;
 }
 
-// Load the first m (< kV) elements of chunk c element by element.
+// The last m elements of a row's last 16 bytes, moved to the front and
+// zero-padded: the row's partial chunk (m is the same for every row).
 template <bool BF16>
-__device__ __forceinline__ void load_partial(const char* row, int c, int m, float* v)
+__device__ __forceinline__ Raw tail_of(Raw r, int m)
 {
+    int words = Layout<BF16>::kV - m;   // leading elements, which belong to the chunk before
     if constexpr (BF16) {
-        const uint16_t* e = reinterpret_cast<const uint16_t*>(row) + (size_t)c * 8;
-        for (int k = 0; k < m; ++k) v[k] = __uint_as_float((uint32_t)e[k] << 16);
-    } else {
-        const float* e = reinterpret_cast<const float*>(row) + (size_t)c * 4;
-        for (int k = 0; k < m; ++k) v[k] = e[k];
+        if (words & 1) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r.w[k] = (r.w[k] >> 16) | (k < 3 ? r.w[k + 1] << 16 : 0u);
+        }
+        words >>= 1;
     }
+    if (words & 1) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r.w[k] = k < 3 ? r.w[k + 1] : 0u;
+    }
+    if (words & 2) {
+        r.w[0] = r.w[2];
+        r.w[1] = r.w[3];
+        r.w[2] = r.w[3] = 0u;
+    }
+    return r;
 }
 
 struct XAcc {
@@ -145,9 +167,12 @@ struct CAcc {
 // d = |x| 2^-e - c in one fused multiply-add (scale = 2^-e): the product is
 // exact for normal values, so d is the rounding of the exact scaled
 // difference, and for near-uniform rows exact (Sterbenz).
+template <int V>
 __device__ __forceinline__ void x_chunk(XAcc& a, const float* v, int m, float c, float scale)
 {
-    for (int k = 0; k < m; ++k) {
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        if (k >= m) continue;
         const float d = fmaf(fabsf(v[k]), scale, -c);
         a.sd += d;
         a.sd2 = fmaf(d, d, a.sd2);
@@ -184,10 +209,13 @@ __device__ __forceinline__ float g2_shannon(float y, float u)
 // Shannon partial sums over m elements for a row shift c > 0 and scale
 // 2^-e (inv_u = 2^-e / c, u = |x| inv_u; inv2 = (1/c) / ln 2 and delta2 =
 // (c (1/c) - 1) / ln 2 give y): sd as for CV^2, sd2 = sum g(u) / ln 2.
+template <int V>
 __device__ __forceinline__ void x_chunk_shannon(XAcc& a, const float* v, int m, float c, float scale,
                                                 float inv_u, float inv2, float delta2)
 {
-    for (int k = 0; k < m; ++k) {
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        if (k >= m) continue;
         const float ax = fabsf(v[k]);
         const float d = fmaf(ax, scale, -c);
         a.sd += d;
@@ -226,21 +254,6 @@ __device__ __forceinline__ void c_chunk(CAcc& a, const Raw& p, const Raw& q)
             a.n2 = fmaf(v, v, a.n2);
         }
     }
-}
-
-// The first m (< elements per chunk) elements of chunk c, zero-padded.
-template <bool BF16>
-__device__ __forceinline__ Raw load_partial_raw(const char* row, int c, int m)
-{
-    Raw r{{0u, 0u, 0u, 0u}};
-    if constexpr (BF16) {
-        const uint16_t* e = reinterpret_cast<const uint16_t*>(row) + (size_t)c * 8;
-        for (int k = 0; k < m; ++k) r.w[k >> 1] |= (uint32_t)e[k] << (16 * (k & 1));
-    } else {
-        const uint32_t* e = reinterpret_cast<const uint32_t*>(row) + (size_t)c * 4;
-        for (int k = 0; k < m; ++k) r.w[k] = e[k];
-    }
-    return r;
 }
 
 __device__ __forceinline__ float wave_sum(float v) { return wave_sum_f32(v); }
@@ -294,11 +307,11 @@ __device__ __forceinline__ Shift make_shift(float c, float scale)
     return h;
 }
 
-template <bool H1>
+template <bool H1, int V>
 __device__ __forceinline__ void x_accumulate(XAcc& xa, const float* v, int m, const Shift& h)
 {
-    if constexpr (H1) x_chunk_shannon(xa, v, m, h.c, h.scale, h.inv_u, h.inv2, h.delta2);
-    else x_chunk(xa, v, m, h.c, h.scale);
+    if constexpr (H1) x_chunk_shannon<V>(xa, v, m, h.c, h.scale, h.inv_u, h.inv2, h.delta2);
+    else x_chunk<V>(xa, v, m, h.c, h.scale);
 }
 
 // Stage I sums of a row from a second read of its bytes: scaled by the power
@@ -344,7 +357,7 @@ __device__ __noinline__ XRow x_reread(const char* row, int D, int lane)
     XAcc xa{0.f, 0.f};
     for (int j = lane; j < D; j += kWave) {
         const float v = elem<BF16>(row, j) * scale;
-        x_accumulate<H1>(xa, &v, 1, r.h);
+        x_accumulate<H1, 1>(xa, &v, 1, r.h);
     }
     r.sd = wave_sum(xa.sd);
     r.sd2 = wave_sum(xa.sd2);
@@ -388,34 +401,40 @@ __device__ __noinline__ CRow cos_reread(const char* pr, const char* qr, int Dc, 
     return r;
 }
 
-template <bool BF16, bool VEC, int UNR, int MODE>
-__global__ __launch_bounds__(256) void score_kernel(ScoreArgs a)
+// How a launch reads its rows.
+constexpr int kBurst = 0;   // UNR chunks of every tensor per lane at once
+constexpr int kPaced = 1;   // one or two loads of a wavefront in flight (see launch_t)
+constexpr int kOdd = 2;     // as kBurst; rows that are no whole number of 16-byte chunks
+
+template <bool BF16, int UNR, int MODE, int READ>
+__global__ __launch_bounds__(kWave) void score_kernel(ScoreArgs a)
 {
     using L = Layout<BF16>;
     constexpr int V = L::kV;
     constexpr bool kX = (MODE & kScoreImp) != 0;    // Eq. (3)-(4) over X
     constexpr bool kC = (MODE & kScoreSim) != 0;    // Eq. (6) over X_pre, X_post
     constexpr bool kH1 = kX && (MODE & kScoreShannon) != 0;   // Shannon variant of Stage I
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
-    if (row >= a.rows) return;   // whole wavefront leaves together
+    constexpr bool ODD = READ == kOdd;
+    // Paced reads: wait for the loads before, so X_pre and X_post go out
+    // together after X's chunk, or singly when they are all that is read.
+    [[maybe_unused]] auto pace = [] {
+        if constexpr (READ == kPaced) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    const int lane = threadIdx.x;
+    const int64_t row = blockIdx.x;
 
     const char* xr = static_cast<const char*>(a.X) + row * (int64_t)a.D * L::kEB;
     const char* pr = static_cast<const char*>(a.P) + row * (int64_t)a.Dc * L::kEB;
     const char* qr = static_cast<const char*>(a.Q) + row * (int64_t)a.Dc * L::kEB;
-    const int nfx = kX ? a.D / V : 0;    // full chunks of X
-    const int nfc = kC ? a.Dc / V : 0;   // full chunks of X_pre / X_post
-    const int nf = nfx > nfc ? nfx : nfc;
+    // Whole chunks, and the elements of a trailing partial chunk.  That one
+    // belongs to lane (index % 64) like any other and is its lane's last.
+    const int nfx = kX ? a.D / V : 0, mx = kX && ODD ? a.D % V : 0;
+    const int nfc = kC ? a.Dc / V : 0, mc = kC && ODD ? a.Dc % V : 0;
+    const int chunks = max(nfx + (mx ? 1 : 0), nfc + (mc ? 1 : 0));
+    const int endx = a.D * L::kEB - 16, endc = a.Dc * L::kEB - 16;   // a row's last 16 bytes
+    const bool short_rows = ODD && ((kX && endx < 0) || (kC && endc < 0));
     // elements in the lanes' first chunks: the sample the shift c averages
     const float n_probe = (float)(a.D < kWave * V ? a.D : kWave * V);
-
-    // A trailing partial chunk belongs to lane (index % 64) like any other and
-    // is that lane's last chunk.
-    const bool tail_x = kX && (a.D % V) && (nfx & (kWave - 1)) == lane;
-    const int mx = a.D - nfx * V;
-    float tx[V];
-    tx[0] = 0.f;
-    if (tail_x) load_partial<BF16>(xr, nfx, mx, tx);
 
     XAcc xa{0.f, 0.f};
     CAcc ca{0.f, 0.f, 0.f};
@@ -433,7 +452,9 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a)
             (uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(fabsf(pv[0])), 0));
         bool same = true;
         float sum = 0.f;
-        for (int k = 0; k < m; ++k) {
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            if (k >= m) continue;
             sum += fabsf(pv[k]);
             same = same && fabsf(pv[k]) == ref;
         }
@@ -442,31 +463,51 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a)
         const float scale = fast_x ? binade_scale(c_raw) : 1.f;
         sh = make_shift(fast_x ? c_raw * scale : 0.f, scale);
     };
-    if (kX && nfx == 0) set_probe(tx, tail_x ? mx : 0);
-
-    for (int j0 = 0; j0 < nf; j0 += kWave * UNR) {   // same trip count for every lane
+    // Every load of a step is issued before anything waits: a lane past the
+    // row's end loads its last 16 bytes (the wavefront's lanes then ask for one
+    // address) instead of skipping the load.  Skipped loads kept their
+    // registers tied to the step before, so the loads went out one or two at a
+    // time, each behind the one before.  The lane of a partial chunk gets it
+    // at the end of those 16 bytes.
+    for (int j0 = 0; j0 < chunks; j0 += kWave * UNR) {   // same trip count for every lane
         Raw rx[UNR], rp[UNR], rq[UNR];
+        if (!short_rows) {
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const int ci = j0 + lane + kWave * u;
-            if (ci < nfx) rx[u] = load_chunk<BF16, VEC>(xr, ci);
-            if (ci < nfc) {
-                rp[u] = load_chunk<BF16, VEC>(pr, ci);
-                rq[u] = load_chunk<BF16, VEC>(qr, ci);
+            for (int u = 0; u < UNR; ++u) {
+                const uint32_t off = (uint32_t)(j0 + lane + kWave * u) * 16;
+                if constexpr (kX) {
+                    pace();
+                    rx[u] = load16(xr, min(off, (uint32_t)endx));
+                }
+                if constexpr (kC) {
+                    pace();
+                    rp[u] = load16(pr, min(off, (uint32_t)endc));
+                    if constexpr (!kX) pace();
+                    rq[u] = load16(qr, min(off, (uint32_t)endc));
+                }
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                const uint32_t off = (uint32_t)(j0 + lane + kWave * u) * 16;
+                if constexpr (kX) rx[u] = endx < 0 ? load_short<BF16>(xr, mx) : load16(xr, min(off, (uint32_t)endx));
+                if constexpr (kC) {
+                    rp[u] = endc < 0 ? load_short<BF16>(pr, mc) : load16(pr, min(off, (uint32_t)endc));
+                    rq[u] = endc < 0 ? load_short<BF16>(qr, mc) : load16(qr, min(off, (uint32_t)endc));
+                }
             }
         }
-        if (j0 == 0 && nfx > 0) {
+        asm volatile("" ::: "memory");   // the loads stay here, none moves down to its use
+        if (kX && j0 == 0) {
             float v[V];
             int m = 0;
+            v[0] = 0.f;
             if (lane < nfx) {
                 unpack<BF16>(rx[0], v);
                 m = V;
-            } else if (tail_x) {
-#pragma unroll
-                for (int k = 0; k < V; ++k) v[k] = tx[k];
+            } else if (ODD && lane == nfx && mx) {
+                unpack<BF16>(endx < 0 ? rx[0] : tail_of<BF16>(rx[0], mx), v);
                 m = mx;
-            } else {
-                v[0] = 0.f;
             }
             set_probe(v, m);
         }
@@ -476,15 +517,20 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a)
             if (ci < nfx) {
                 float v[V];
                 unpack<BF16>(rx[u], v);
-                x_accumulate<kH1>(xa, v, V, sh);
+                x_accumulate<kH1, V>(xa, v, V, sh);
             }
             if (ci < nfc) c_chunk<BF16>(ca, rp[u], rq[u]);
+            if constexpr (ODD) {
+                if (kX && mx && ci == nfx) {
+                    float v[V];
+                    unpack<BF16>(endx < 0 ? rx[u] : tail_of<BF16>(rx[u], mx), v);
+                    x_accumulate<kH1, V>(xa, v, mx, sh);
+                }
+                if (kC && mc && ci == nfc)
+                    c_chunk<BF16>(ca, endc < 0 ? rp[u] : tail_of<BF16>(rp[u], mc),
+                                  endc < 0 ? rq[u] : tail_of<BF16>(rq[u], mc));
+            }
         }
-    }
-    if (tail_x) x_accumulate<kH1>(xa, tx, mx, sh);
-    if (kC && a.Dc % V && (nfc & (kWave - 1)) == lane) {
-        const int m = a.Dc - nfc * V;
-        c_chunk<BF16>(ca, load_partial_raw<BF16>(pr, nfc, m), load_partial_raw<BF16>(qr, nfc, m));
     }
 
     float sd = 0.f, sd2 = 0.f, s = 0.f;
@@ -562,45 +608,70 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a)
 
 // One wavefront per workgroup: the finest scheduling grain spreads rows evenly
 // over the 256 CUs (measured 128 us vs 136 us with four-wavefront groups on
-// 64 x 576 x 4096 bf16 rows, the latter equal to a plain read of the bytes).
-template <bool BF16, bool VEC, int MODE>
+// 64 x 576 x 4096 bf16 rows).
+//
+// Small launches are bound by the latency of their loads, so a wavefront
+// issues four chunks of every tensor at once (kBurst): 576 x 4096 bf16 rows
+// 12.1 -> 9.0 us a call, 20000 x 1152 33.5 -> 21.4 us, against loads that
+// waited for one another.  Large launches are bound by HBM, and there more
+// bytes in flight than the round trip needs (about 27 KB a CU) only queue
+// before the memory: 73728 x 4096 bf16 rows take 266 us with 32 wavefronts of
+// 12 KB in flight, 257 us with 12 of 3 KB, 253 us (7.17 TB/s) with 20 of 1-2
+// KB, 263 us with 8 of 3 KB.  So they are paced: a wavefront keeps X's chunk,
+// then X_pre's and X_post's in flight, with 20 wavefronts a CU (8 KB of unused
+// LDS each), or 16 from 1.5 GB on (46080 x 4096 rows, 1.1 GB: 158 us with 20,
+// 161 with 16; 73728 rows 255 and 253, 150000 rows 532 and 522); the states
+// alone one chunk at a time with 28 (166 against 174 us in bursts), X alone
+// with all 32 (86 against 89 us).  The line lies where
+// both measure the same: rows of 5 KB (3 KB rows: 118 paced against 123 us in
+// bursts, 4 KB 111 against 107, 2 KB 122 against 107) and 128 MB of reads (8 KB
+// rows: 75 MB 13.9 against 11.8 us, 113 MB 20.2 against 20.3, 226 MB 34.5
+// against 34.9; X alone from 512 MB on).
+constexpr int64_t kPacedRow = 5 << 10;
+constexpr int64_t kPacedBytes = 128 << 20, kPacedBytesX = 512 << 20;
+constexpr int64_t kPacedLess = (int64_t)3 << 29;
+
+template <bool BF16, int MODE>
 hipError_t launch_t(const ScoreArgs& a, hipStream_t s)
 {
-    constexpr int kThreads = 64;
-    constexpr int kRowsPerBlock = kThreads / kWave;
-    const int64_t blocks = (a.rows + kRowsPerBlock - 1) / kRowsPerBlock;
-    if (blocks <= 0) return hipSuccess;
-    // The Shannon terms need more registers per element: three chunks of each
-    // tensor in flight (91 VGPRs, five wavefronts per SIMD) measured fastest
-    // on 64 x 576 x 4096 bf16 rows, 131 us against 145 us with two (six
-    // wavefronts per SIMD) and 134 us with four (four per SIMD).
-    constexpr int kUnroll = (MODE & kScoreShannon) ? 3 : 4;
-    hipLaunchKernelGGL((score_kernel<BF16, VEC, kUnroll, MODE>), dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
+    if (a.rows <= 0) return hipSuccess;
+    constexpr int V = Layout<BF16>::kV, kEB = Layout<BF16>::kEB;
+    constexpr bool kX = (MODE & kScoreImp) != 0, kC = (MODE & kScoreSim) != 0;
+    const dim3 grid((unsigned)a.rows), block(kWave);
+    const int64_t row = (int64_t)(kX ? a.D : a.Dc) * kEB;
+    const int64_t total = a.rows * row * (kX ? (kC ? 3 : 1) : 2);
+    if ((kX && a.D % V) || (kC && a.Dc % V)) {
+        hipLaunchKernelGGL((score_kernel<BF16, 4, MODE, kOdd>), grid, block, 0, s, a);
+    } else if (row >= kPacedRow && total >= (kC ? kPacedBytes : kPacedBytesX) && !(kX && kC && a.D != a.Dc)) {
+        const int pad = !kX ? 5440 : !kC ? 0 : total < kPacedLess ? 8192 : 10240;
+        hipLaunchKernelGGL((score_kernel<BF16, 1, MODE, kPaced>), grid, block, pad, s, a);
+    } else {
+        hipLaunchKernelGGL((score_kernel<BF16, 4, MODE, kBurst>), grid, block, 0, s, a);
+    }
     return hipGetLastError();
 }
 
-template <bool BF16, bool VEC>
+template <bool BF16>
 hipError_t launch_m(const ScoreArgs& a, int mode, hipStream_t s)
 {
     constexpr int I = kScoreImp, S = kScoreSim, H = kScoreShannon;
     switch (mode) {
-    case I: return launch_t<BF16, VEC, I>(a, s);
-    case S: return launch_t<BF16, VEC, S>(a, s);
-    case I | S: return launch_t<BF16, VEC, I | S>(a, s);
-    case I | H: return launch_t<BF16, VEC, I | H>(a, s);
-    default: return launch_t<BF16, VEC, I | S | H>(a, s);
+    case I: return launch_t<BF16, I>(a, s);
+    case S: return launch_t<BF16, S>(a, s);
+    case I | S: return launch_t<BF16, I | S>(a, s);
+    case I | H: return launch_t<BF16, I | H>(a, s);
+    default: return launch_t<BF16, I | S | H>(a, s);
     }
 }
 
 }  // namespace
 
-hipError_t launch_score(const ScoreArgs& a, bool bf16, bool vec, int mode, hipStream_t s)
+hipError_t launch_score(const ScoreArgs& a, bool bf16, int mode, hipStream_t s)
 {
     const int base = mode & ~kScoreShannon;
     if (base != kScoreImp && base != kScoreSim && base != (kScoreImp | kScoreSim)) return hipErrorInvalidValue;
     if ((mode & kScoreShannon) && !(mode & kScoreImp)) mode &= ~kScoreShannon;
-    if (bf16) return vec ? launch_m<true, true>(a, mode, s) : launch_m<true, false>(a, mode, s);
-    return vec ? launch_m<false, true>(a, mode, s) : launch_m<false, false>(a, mode, s);
+    return bf16 ? launch_m<true>(a, mode, s) : launch_m<false>(a, mode, s);
 }
 
 }  // namespace tr

@@ -1236,6 +1236,7 @@ __device__ __forceinline__ uint32_t rank_in(const uint64_t* list, uint32_t beg, 
 }
 
 typedef uint32_t u32x4s __attribute__((ext_vector_type(4)));
+typedef u32x4s u32x4s_any __attribute__((aligned(2)));   // 16 bytes at any element
 
 __global__ __launch_bounds__(kSmallSelectN) void select_small_kernel(SelectArgs a)
 {
@@ -1374,10 +1375,12 @@ __global__ __launch_bounds__(kSmallSelectN) void select_small_kernel(SelectArgs 
     const char* X = static_cast<const char*>(a.gX);
     char* out = static_cast<char*>(a.gout);
     const int64_t rb = a.grow_bytes;
-    if (a.gvec) {
-        // Chunk j = r * cpr + c of the share, walked with (r, c) carried
+    if (rb >= 16) {
+        // Pieces of 16 bytes; a row's last one is its last 16 bytes (they
+        // overlap the piece before when the row is no multiple of 16).  Piece j =
+        // r * cpr + c of the share, walked with (r, c) carried
         // from step to step (no division per chunk).
-        const uint32_t cpr = (uint32_t)(rb / 16);
+        const uint32_t cpr = (uint32_t)((rb + 15) / 16), last = (uint32_t)(rb - 16);
         const uint32_t rows = (uint32_t)(s1 - s0);
         const uint32_t qT = (uint32_t)T / cpr, mT = (uint32_t)T % cpr;
         uint32_t r = (uint32_t)tid / cpr, c = (uint32_t)tid % cpr;
@@ -1393,7 +1396,7 @@ __global__ __launch_bounds__(kSmallSelectN) void select_small_kernel(SelectArgs 
                     const uint32_t k = kept[s0 + (int)r];
                     const uint32_t tk = k < (uint32_t)N ? k : 0u;   // always a filled slot
                     v[u] = __builtin_nontemporal_load(
-                        reinterpret_cast<const u32x4s*>(X + (int64_t)(d.row_off + (int)tk) * rb) + c);
+                        reinterpret_cast<const u32x4s_any*>(X + (int64_t)(d.row_off + (int)tk) * rb + min(c * 16, last)));
                 }
                 c += mT;
                 r += qT;
@@ -1406,7 +1409,8 @@ __global__ __launch_bounds__(kSmallSelectN) void select_small_kernel(SelectArgs 
             for (int u = 0; u < kUnr; ++u) {
                 if (rr[u] < rows)
                     __builtin_nontemporal_store(
-                        v[u], reinterpret_cast<u32x4s*>(out + (int64_t)(d.out_off + s0 + (int)rr[u]) * rb) + cc[u]);
+                        v[u], reinterpret_cast<u32x4s_any*>(out + (int64_t)(d.out_off + s0 + (int)rr[u]) * rb +
+                                                            min(cc[u] * 16, last)));
             }
         }
     } else if (a.gelem == 2) {
