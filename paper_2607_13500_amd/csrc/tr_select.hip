@@ -1,8 +1,8 @@
-// Per-image selection (Algorithm 1 after the scores), everything resident in
-// LDS.  Images of at most kSmallSelectN tokens take select_small_kernel (one
-// token per thread, both stages ranked in the same passes; described where
-// it is defined).  Larger images take select_kernel: one 1024-thread
-// workgroup per image, or several sharing the ranking of a large image.
+// Per-image selection (Algorithm 1 after the scores).  Images of at most
+// kSmallSelectN tokens take select_small_kernel (one token per thread, both
+// stages ranked in the same passes; described where it is defined).  Larger
+// images take select_kernel: one 1024-thread workgroup per image, or several
+// sharing the ranking of a large one.
 //
 // Keys are fp32 scores mapped to order-preserving u32 (-0 == +0).  Stage I
 // keeps the K1 smallest Stage I keys (ties: lower index); Stage II orders
@@ -10,35 +10,36 @@
 // 0, t, ..., (K2-1) t (or floor(j R / K2) in the real-interval variant); the
 // output lists X^imp U X^div in token order.
 //
-// Stage I buckets the keys by value (1024 equal-width buckets over their
-// range, one pass) and a DPP scan finds the bucket holding the K1-th smallest
-// key.  One more pass keeps every lower bucket and lists the members of that
-// boundary bucket; one thread per listed member then counts the members
-// smaller than itself in (key, index) order and keeps it if that rank is
-// below the remaining budget.  When the boundary bucket holds more than 128
-// keys (or the range is not finite), Stage I instead narrows a bucket
-// {k : (k & pmask) == prefix} that contains the K1-th key with 8-bit digit
-// passes over the highest still-undecided bits in which some key differs
-// (bytes no key varies in cost nothing): each pass is a histogram (ballot
-// "same digit" masks, one LDS atomic per distinct digit per tile) and a DPP
-// scan that picks the digit holding the K1-th key.  It stops when
-//   - the bucket holds a single key value T: keys < T are kept, then the first
-//     keys == T in token order (ordered ballot counts), or
-//   - the bucket holds at most 128 keys: ranked as above.
-// Stage II buckets X^rem by value, 1024 buckets of equal width over the
-// [min, max] of its keys, in one pass; every token's rank in the sorted
-// X^rem is then its bucket's start plus the number of its bucket's members
-// smaller in (key, index) order, counted exactly: per token for small images,
-// a whole bucket per wavefront for large ones (shared by several workgroups
-// that each rank a fixed share of the buckets).  If a bucket exceeds 256
-// tokens or the range is not finite, Stage II falls back to a stable LSD radix
-// sort of the 16-bit indices of X^rem (ordered compaction first, digits looked
-// up by index, per-wavefront scatter offsets, passes over constant bytes
-// skipped).
+// select_kernel keeps the image's keys in LDS.  One compute unit walks all
+// of them, so its passes are bound by VALU issue (72 wavefront tiles on each
+// SIMD for 18432 tokens) and are few: two over all tokens, then some over the
+// tokens a workgroup ranks.
 //
-// Every wavefront owns a contiguous, 64-aligned range of tokens for the
-// ordered steps (tie marking, compaction, output), so all results are exact
-// and deterministic.
+// Stage I looks for T, the K1-th smallest (key, index).  A round histograms the
+// keys of a range into 1024 equal ranges of the order-preserving key and counts
+// the keys below it; the next range is the one that holds T, so a round
+// narrows it 512-fold or more whatever the values are.  The first range comes
+// from 64 sampled keys around rank 64 K1 / N (a miss costs rounds over the side
+// it names), and its histogram is taken as the keys arrive from memory.  At
+// kMembers keys or fewer the range is left to the next pass; when one key value
+// is left, the indices of its tokens are narrowed the same way.
+//
+// The second pass marks the keys below the range as X^imp, lists the range's
+// members (ranked by counting: X^imp or not) and finds the workgroup's own
+// tokens of X^rem: workgroup p of G on an image owns the tokens between samples
+// p kSample / G and (p + 1) kSample / G of kSample sampled Stage II keys
+// ((key, index) pairs where a sampled key repeats, so that equal keys are
+// shared out too); G = 1 owns them all.  The tokens of X^rem below its own
+// are counted, its own histogrammed into 1024 value buckets (bucket_of is
+// non-decreasing in the key) and listed in bucket order, and a thread per listed
+// token counts the members of its bucket smaller in (key, index) order.  Its
+// rank in X^rem is the three counts' sum: exact, whatever the samples.  If
+// many tokens share a bucket (kCountFixed) the own tokens are sorted instead, by a stable LSD radix sort of 16-bit indices (ordered compaction
+// first, digits looked up by index, per-wavefront scatter offsets, passes over
+// constant bytes skipped).
+//
+// In the output step every wavefront owns a contiguous, 64-aligned range of
+// tokens; all results are exact and deterministic.
 #include <type_traits>
 
 #include "tr_internal.h"
@@ -49,44 +50,49 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kW = kThreads / kWave;
-constexpr uint32_t kCountLimit = 128;    // Stage I: count exactly inside buckets this small
-constexpr int kBuckets = kThreads;       // Stage II: value buckets (one per thread in the scan)
-constexpr uint32_t kBucketLimit = 256;   // Stage II: largest bucket ranked by counting
-constexpr int kDenseRem = 4096;          // Stage II: rank whole buckets per wavefront from here
+constexpr int kMaxSlots = 19;            // tokens per thread: images of at most 19456
+constexpr int kUnr = 4;                  // tokens per thread a pass reads before it works on them
+constexpr int kBuckets = kThreads;       // buckets of a histogram (one per thread in the scan)
+constexpr uint32_t kMembers = 256;       // Stage I: list and rank the members of ranges this small
+// Stage II: own tokens are ranked by counting while the squares of their buckets'
+// sizes (the LDS reads) sum to at most kCountFixed + kCountPer for each of them:
+// 1500 tokens in two buckets of 750 took 38 us to count, and sorting takes
+// about 10 us for each thousand tokens.
+constexpr uint32_t kCountFixed = 150000, kCountPer = 300;
+constexpr int kSample = 128;             // Stage II: samples that share out an image
+constexpr int kShareRem = 4096;          // Stage II: share images with this many remaining tokens
+constexpr int kListN = 2 * kShareRem;    // images below this have LDS for every token as a pair
 constexpr int kMaxSplitGroups = 64;      // most workgroups sharing the ranking of one large image
-constexpr uint16_t kNoBucket = 0xffff;   // Stage II bucket index of a token not in X^rem
-static_assert(kCountLimit <= (uint32_t)kThreads && kCountLimit % kWave == 0,
-              "one thread per listed Stage I member, in whole wavefronts");
-static_assert((kMaxSplitGroups & (kMaxSplitGroups - 1)) == 0 && kMaxSplitGroups * kW <= kBuckets,
-              "split ownership is a mask; every wavefront of the groups owns a bucket");
-static_assert(kDenseRem / 2 >= 2 * kWave * kW, "dense ranking's pairs fit above the X^rem list");
+static_assert(kMembers <= (uint32_t)kThreads, "one thread per listed Stage I member");
+static_assert((kMaxSplitGroups & (kMaxSplitGroups - 1)) == 0 && kMaxSplitGroups * 2 <= kSample,
+              "two samples or more to a workgroup");
+static_assert(kShareRem >= 4 * kSample, "samples of a shared image are distinct tokens");
+static_assert(kMaxSlots <= 32 && kMaxSlots * kThreads <= 65535, "16-bit indices, and products of ranks below 2^32");
 
 // ---- LDS layout (same arithmetic on host and device) -----------------------
 struct LdsLayout {
-    size_t ks, ki, bimp, bsel, area, slots, misc, comp, total;
-    bool has_comp;
+    size_t ks, ki, bimp, bsel, area, slots, misc, list, list_bytes, total;
 };
 
 __host__ __device__ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) & ~(a - 1); }
 
 //   ks    u32[n]        Stage II keys by token index
-//   ki    u32[n]        Stage I keys; after Stage I the same bytes hold the
-//                       u16 bucket list of X^rem (lower half) and each
-//                       token's u16 bucket (upper half), then the dense
-//                       ranking's per-wavefront pairs above the list; or the
-//                       two u16[n] index buffers of the radix sort
-//   bimp  u32[nw]       X^imp bitmap (nw = 2 ceil(n / 64))
+//   ki    u32[n]        Stage I keys; once X^imp is known the list of the own
+//                       tokens (below), or the two u16[n] index buffers of the
+//                       radix sort
+//   bimp  u32[nw]       X^imp bitmap (nw = 2 ceil(n / 64)); the radix sort of a
+//                       shared image: the tokens it leaves out
 //   bsel  u32[nw]       X^imp U X^div bitmap
-//   area  u32[2048]     16-byte aligned, reused by phase:
-//                         Stage I:  [0, 512) two 256-bin digit histograms,
-//                                   [512, 768) u64[128] bucket members
-//                         Stage II: [0, 1024) bucket counts, [1024, 2048)
-//                                   bucket cursors; or u16[256][W] digit
-//                                   counts / offsets of the radix sort
+//   area  u32[2048]     16-byte aligned: [0, 1024) histogram, [1024, 2048) by
+//                       phase the samples (kS*), Stage I's
+//                       members u64[kMembers], Stage II's bucket cursors; or
+//                       u16[256][W] digit counts / offsets of the radix sort
 //   slots u32[8][W]     per-wavefront partial values, one row per use
-//   misc  u32[16]       broadcast slots and counters
-//   comp  u64[n]        only for n < kDenseRem: X^rem as (key << 32 | index)
-//                       in bucket order, for the per-token ranking
+//   misc  u32[16]       broadcast words (kM*)
+//   list  list_bytes    the own tokens in bucket order: u64 (key << 32 | index)
+//                       if they fit, else u16 indices.  n < kListN: a
+//                       region of u64[n], else the bytes of ki (a share of a
+//                       large image is far smaller)
 __host__ __device__ inline LdsLayout lds_layout(int n)
 {
     LdsLayout L;
@@ -102,32 +108,45 @@ __host__ __device__ inline LdsLayout lds_layout(int n)
     o += 4 * nw;
     o = align_up(o, 16);
     L.area = o;
-    o += 4 * 2048;
+    o += 4 * 2 * kBuckets;
     L.slots = o;
     o += 4 * 8 * kW;
     L.misc = o;
     o += 4 * 16;
-    L.has_comp = n < kDenseRem;
-    L.comp = 0;
-    if (L.has_comp) {
-        o = align_up(o, 16);
-        L.comp = o;
-        o += 8 * (size_t)n;
+    if (n < kListN) {
+        L.list = o;
+        L.list_bytes = 8 * (size_t)n;
+        o += L.list_bytes;
+    } else {
+        L.list = align_up(L.ki, 8);
+        L.list_bytes = 4 * (size_t)n - (L.list - L.ki);
     }
     L.total = o;
     return L;
 }
 
-// LDS a launch needs for images of at most nmax tokens: the layout's size is
-// not monotonic in n (comp exists only below kDenseRem), so the largest over
-// n <= nmax.
+// LDS a launch needs for images of at most nmax tokens: the largest layout of
+// any n <= nmax (it is not monotonic at kListN).
 __host__ __device__ inline size_t launch_lds(int nmax)
 {
     const size_t big = lds_layout(nmax).total;
-    if (nmax < kDenseRem) return big;
-    const size_t small = lds_layout(kDenseRem - 1).total;
+    if (nmax < kListN) return big;
+    const size_t small = lds_layout(kListN - 1).total;
     return big > small ? big : small;
 }
+
+// Words of area + 1024 while samples are ranked.
+constexpr int kSRows = 0;      // u64[2][64]: the two kinds' 64 samples
+constexpr int kSRanks = 256;   // u16[8][kSample]: partial ranks
+constexpr int kSSorted = 256 + 4 * kSample;   // u32[kSample]: sampled Stage II keys in order
+static_assert(kSSorted >= 2 * (int)kMembers && kSSorted + kSample <= kBuckets, "above Stage I's members, in the area");
+
+// Words of misc.
+constexpr int kMBracket = 0;   // Stage I's sampled range (2 keys)
+constexpr int kMQuant = 2;     // Stage II's value range (2 keys)
+constexpr int kMRound = 4;     // a round's bucket, the rank inside it, its size
+constexpr int kMCount = 7;     // listed members
+constexpr int kMOwn = 8;       // first pair owned, first pair not owned any more (2 u64)
 
 // ---- helpers -------------------------------------------------------------------
 // IEEE order -> unsigned order; -0 and +0 map to the same key.
@@ -142,6 +161,8 @@ __device__ __forceinline__ float key_value(uint32_t k)
 {
     return __uint_as_float((k & 0x80000000u) ? (k ^ 0x80000000u) : ~k);
 }
+
+__device__ __forceinline__ uint64_t pair_of(uint32_t key, uint32_t i) { return ((uint64_t)key << 32) | i; }
 
 __device__ __forceinline__ uint64_t lanes_below(int lane) { return (1ull << lane) - 1ull; }
 
@@ -173,42 +194,6 @@ __device__ __forceinline__ void put_tile_bits(uint32_t* bm, int base, uint64_t b
     if (lane == 0) *reinterpret_cast<uint64_t*>(bm + (base >> 5)) = bits;
 }
 
-// bsel's words of tile `base` = bimp's words | bits.
-__device__ __forceinline__ void put_tile_union(uint32_t* bsel, const uint32_t* bimp, int base,
-                                               uint64_t bits, int lane)
-{
-    if (lane == 0)
-        *reinterpret_cast<uint64_t*>(bsel + (base >> 5)) =
-            *reinterpret_cast<const uint64_t*>(bimp + (base >> 5)) | bits;
-}
-
-// A wavefront's passes over its token range read kTileUnr tiles of 64 from
-// LDS before working on any of them, so the reads overlap.
-constexpr int kTileUnr = 4;
-
-// Keys base + 64 u + lane of v (u < kTileUnr); from `end` on, the key of
-// 0.0f, so that bucket arithmetic on them stays finite (callers mask them).
-__device__ __forceinline__ void load_tiles(const uint32_t* v, int base, int end, int lane,
-                                           uint32_t (&out)[kTileUnr])
-{
-#pragma unroll
-    for (int u = 0; u < kTileUnr; ++u) {
-        const int i = base + u * kWave + lane;
-        out[u] = i < end ? v[i] : 0x80000000u;
-    }
-}
-
-// Whether each of the same tokens is in X^rem (before `end`, not in bimp).
-__device__ __forceinline__ void rem_tiles(const uint32_t* bimp, int base, int end, int lane,
-                                          bool (&out)[kTileUnr])
-{
-#pragma unroll
-    for (int u = 0; u < kTileUnr; ++u) {
-        const int i = base + u * kWave + lane;
-        out[u] = i < end && !bit_of(bimp, i);
-    }
-}
-
 // Contiguous 64-aligned token range of wavefront w.
 __device__ __forceinline__ void wave_range(int n, int w, int& beg, int& end)
 {
@@ -232,13 +217,7 @@ __device__ __forceinline__ uint32_t max_all(const uint32_t* row, int lane)
     return wave_max_u32(lane < kW ? row[lane] : 0u);
 }
 
-__device__ __forceinline__ uint32_t or_all(const uint32_t* row, int lane)
-{
-    return wave_or_u32(lane < kW ? row[lane] : 0u);
-}
-
-// Exclusive prefix over wavefronts of a per-wavefront count (each row of
-// slots is used once per kernel).
+// Exclusive prefix over wavefronts of a per-wavefront count.
 __device__ __forceinline__ uint32_t wave_prefix(uint32_t count, uint32_t* row)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -266,313 +245,6 @@ __device__ __forceinline__ Img image_of(const SelectArgs& a, int local)
     return Img{d.row_off, d.n, d.k1, d.k2, d.t, d.out_off};
 }
 
-// ---- phases ------------------------------------------------------------------
-// Load the image's keys (all global loads of a batch issued before the LDS
-// stores), zero `nzero` words at `zero`, and return the bits in which some key
-// differs from token 0's key (each kind) and the range of the Stage I keys.
-struct KeyStats {
-    uint32_t k0i, VI, VS, kimin, kimax;
-};
-
-__device__ KeyStats load_keys(const SelectArgs& a, const Img& d, uint32_t* ki, uint32_t* ks,
-                              uint32_t* zero, int nzero, uint32_t* slots)
-{
-    constexpr int kUnr = 8;   // keys of each kind in flight per thread
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    const int N = d.n;
-    KeyStats r;
-    r.k0i = order_key(a.key_imp[d.row_off]);
-    const uint32_t k0s = order_key(a.key_s[d.row_off]);
-    uint32_t vi = 0, vs = 0, nlo = 0, hi = 0;
-    for (int i0 = tid; i0 < N; i0 += kUnr * kThreads) {
-        float fi[kUnr], fs[kUnr];
-#pragma unroll
-        for (int u = 0; u < kUnr; ++u) {
-            const int i = i0 + u * kThreads;
-            if (i < N) {
-                fi[u] = a.key_imp[d.row_off + i];
-                fs[u] = a.key_s[d.row_off + i];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kUnr; ++u) {
-            const int i = i0 + u * kThreads;
-            if (i < N) {
-                const uint32_t qi = order_key(fi[u]), qs = order_key(fs[u]);
-                ki[i] = qi;
-                ks[i] = qs;
-                vi |= qi ^ r.k0i;
-                vs |= qs ^ k0s;
-                nlo = max(nlo, ~qi);
-                hi = max(hi, qi);
-            }
-        }
-    }
-    for (int i = tid; i < nzero; i += kThreads) zero[i] = 0;
-    vi = wave_or_u32(vi);
-    vs = wave_or_u32(vs);
-    nlo = wave_max_u32(nlo);
-    hi = wave_max_u32(hi);
-    if (lane == 0) {
-        slots[w] = vi;
-        slots[kW + w] = vs;
-        slots[2 * kW + w] = nlo;
-        slots[3 * kW + w] = hi;
-    }
-    __syncthreads();
-    r.VI = or_all(slots, lane);
-    r.VS = or_all(slots + kW, lane);
-    nlo = max_all(slots + 2 * kW, lane);
-    hi = max_all(slots + 3 * kW, lane);
-    r.kimin = ~nlo;
-    r.kimax = hi;
-    return r;
-}
-
-// Append (key, index) of the lanes with `member` set to `list`, reserving the
-// wavefront's slots with one atomic on the counter `cnt`.
-__device__ __forceinline__ void append_member(bool member, uint32_t key, int i, uint64_t* list,
-                                              uint32_t* cnt, int lane)
-{
-    const uint64_t bm = __ballot(member);
-    if (!bm) return;
-    const int leader = (int)__ffsll((long long)bm) - 1;
-    uint32_t b0 = 0;
-    if (lane == leader) b0 = atomicAdd(cnt, (uint32_t)__popcll(bm));
-    b0 = (uint32_t)__builtin_amdgcn_readlane((int)b0, leader);
-    if (member) list[b0 + __popcll(bm & lanes_below(lane))] = ((uint64_t)key << 16) | (uint32_t)i;
-}
-
-// Keep the `need` smallest of the m listed (key, index) members of the Stage I
-// boundary bucket: thread j counts the entries below entry j (the entries are
-// distinct, so the counts are the ranks) and sets the member's bits.  With ks
-// given, the Stage II keys of the members left in X^rem are folded into the
-// per-wavefront range rows (~min, max) of wavefronts 0 and 1.
-__device__ void keep_ranked_members(const uint64_t* list, uint32_t m, uint32_t need, uint32_t* bimp,
-                                    uint32_t* bsel, const uint32_t* ks, uint32_t* row_lo,
-                                    uint32_t* row_hi)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    uint32_t nlo = 0, hi = 0;
-    if (tid < (int)m) {
-        const uint64_t mine = list[tid];
-        uint32_t r = 0;
-        for (uint32_t j = 0; j < m; ++j) r += list[j] < mine ? 1u : 0u;
-        const int i = (int)(mine & 0xffffu);
-        if (r < need) {
-            atomicOr(&bimp[i >> 5], 1u << (i & 31));
-            atomicOr(&bsel[i >> 5], 1u << (i & 31));
-        } else if (ks) {
-            nlo = ~ks[i];
-            hi = ks[i];
-        }
-    }
-    if (ks && tid < (int)kCountLimit) {   // whole wavefronts: every lane takes part
-        nlo = wave_max_u32(nlo);
-        hi = wave_max_u32(hi);
-        if (lane == 0) {
-            row_lo[w] = max(row_lo[w], nlo);
-            row_hi[w] = max(row_hi[w], hi);
-        }
-    }
-}
-
-// Stage I digit passes (see the file comment).  On return the bucket
-// {k : (k & pmask) == prefix} holds m keys and the K1-th smallest key overall
-// is its need-th smallest; resolved means the bucket is a single key value.
-__device__ void stage1_narrow(const uint32_t* ki, int N, uint32_t VI, uint32_t* hsh, uint32_t* misc,
-                              uint32_t limit, uint32_t& prefix, uint32_t& pmask, uint32_t& need,
-                              uint32_t& m, bool& resolved)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    int beg, end;
-    wave_range(N, w, beg, end);
-    resolved = false;
-    for (int p = 0;; ++p) {
-        const uint32_t vrem = VI & ~pmask;
-        if (vrem == 0) {
-            resolved = true;
-            return;
-        }
-        if (m <= limit) return;
-        const int hb = 31 - __clz((int)vrem);
-        const int lo = hb >= 7 ? hb - 7 : 0;
-        const uint32_t win = (hb == 31 ? 0xffffffffu : ((2u << hb) - 1u)) & ~((1u << lo) - 1u);
-        uint32_t* H = hsh + (p & 1) * 256;
-        if (tid < 256) hsh[((p + 1) & 1) * 256 + tid] = 0;   // the next pass's histogram
-        for (int base = beg; base < end; base += kWave) {
-            const int i = base + lane;
-            bool act = i < end;
-            const uint32_t key = act ? ki[i] : 0u;
-            act = act && ((key & pmask) == prefix);
-            const uint32_t dg = (key >> lo) & 255u;
-            const uint64_t mm = same_digit(dg, act);
-            if (act && is_leader(mm, lane)) atomicAdd(&H[dg], (uint32_t)__popcll(mm));
-        }
-        __syncthreads();
-        if (w == 0) {
-            const uint4 c4 = *reinterpret_cast<const uint4*>(H + lane * 4);
-            const uint32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
-            const uint32_t sum = c[0] + c[1] + c[2] + c[3];
-            uint32_t run = wave_scan_add(sum) - sum;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (run < need && need <= run + c[q]) {
-                    misc[0] = (uint32_t)(lane * 4 + q);
-                    misc[1] = need - run;
-                    misc[2] = c[q];
-                }
-                run += c[q];
-            }
-        }
-        __syncthreads();
-        prefix |= misc[0] << lo;
-        need = misc[1];
-        m = misc[2];
-        pmask |= win;
-    }
-}
-
-// Value bucket of a key: floor((v - fmin) * scale) clamped to the last
-// bucket, non-decreasing in the key.  Callers guarantee a finite width and
-// scale, so for keys in [fmin, fmax] the product is finite and in range.
-__device__ __forceinline__ int value_bucket(uint32_t key, float fmin, float scale)
-{
-    return min(kBuckets - 1, (int)((key_value(key) - fmin) * scale));
-}
-
-// Stage I by one bucketing pass: 1024 buckets of equal width over the key
-// range; tokens in buckets below the one holding the K1-th key are kept, and
-// members of that bucket (at most kCountLimit of them) are kept when fewer
-// than the remaining budget of members precede them in (key, index) order.
-// H (kBuckets words) must be zero; list holds kCountLimit u64; misc[8] must be
-// 0.  On success row_lo / row_hi hold per-wavefront (~min, max) of the Stage II
-// keys of X^rem, so Stage II needs no range pass of its own.  Returns false
-// (having written only H, misc[0..2] and `row`) when the range is not finite
-// or the boundary bucket is larger.
-__device__ bool stage1_bucket(const uint32_t* ki, const uint32_t* ks, int N, uint32_t K1,
-                              uint32_t kimin, uint32_t kimax, uint32_t* H, uint64_t* list,
-                              uint32_t* misc, uint32_t* row, uint32_t* row_lo, uint32_t* row_hi,
-                              uint32_t* bimp, uint32_t* bsel)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    int beg, end;
-    wave_range(N, w, beg, end);
-    const float fmin = key_value(kimin);
-    const float width = key_value(kimax) - fmin;
-    if (!(width > 0.f) || !(width < 3.0e38f)) return false;
-    const float scale = (float)kBuckets / width;
-    if (!(scale < 3.0e38f)) return false;   // a range of denormals: bucket arithmetic would overflow
-    for (int base = beg; base < end; base += kTileUnr * kWave) {
-        uint32_t k[kTileUnr];
-        load_tiles(ki, base, end, lane, k);
-#pragma unroll
-        for (int u = 0; u < kTileUnr; ++u) {
-            const int dg = value_bucket(k[u], fmin, scale);
-            if (base + u * kWave + lane < end) atomicAdd(&H[dg], 1u);
-        }
-    }
-    __syncthreads();
-    {   // thread tid owns bucket tid: find the bucket holding the K1-th key
-        const uint32_t c = H[tid];
-        const uint32_t inc = wave_scan_add(c);
-        if (lane == kWave - 1) row[w] = inc;
-        __syncthreads();
-        const uint32_t start = inc - c + sum_before(row, w, lane);
-        if (start < K1 && K1 <= start + c) {
-            misc[0] = (uint32_t)tid;
-            misc[1] = K1 - start;
-            misc[2] = c;
-        }
-    }
-    __syncthreads();
-    const int dstar = (int)misc[0];
-    const uint32_t need = misc[1];
-    if (misc[2] > kCountLimit) return false;
-    uint32_t nlo = 0, hi = 0;   // Stage II key range of the tokens above the boundary bucket
-    for (int base = beg; base < end; base += kTileUnr * kWave) {
-        uint32_t k[kTileUnr], q[kTileUnr];
-        load_tiles(ki, base, end, lane, k);
-        load_tiles(ks, base, end, lane, q);
-#pragma unroll
-        for (int u = 0; u < kTileUnr; ++u) {
-            const int tb = base + u * kWave;
-            if (tb >= end) break;   // the next tiles belong to the next wavefront
-            const int i = tb + lane;
-            const int dv = value_bucket(k[u], fmin, scale);
-            const int dg = i < end ? dv : kBuckets;
-            const uint64_t bt = __ballot(dg < dstar);
-            put_tile_bits(bimp, tb, bt, lane);
-            put_tile_bits(bsel, tb, bt, lane);
-            append_member(dg == dstar, k[u], i, list, &misc[8], lane);
-            const bool above = i < end && dg > dstar;
-            nlo = max(nlo, above ? ~q[u] : 0u);
-            hi = max(hi, above ? q[u] : 0u);
-        }
-    }
-    nlo = wave_max_u32(nlo);
-    hi = wave_max_u32(hi);
-    if (lane == 0) {
-        row_lo[w] = nlo;
-        row_hi[w] = hi;
-    }
-    __syncthreads();
-    keep_ranked_members(list, misc[8], need, bimp, bsel, ks, row_lo, row_hi);
-    return true;
-}
-
-// Stage I marking with a resolved threshold key T: keys < T, then the first
-// `need` keys == T in token order.
-__device__ void stage1_mark_resolved(const uint32_t* ki, int N, uint32_t T, uint32_t need,
-                                     uint32_t* bimp, uint32_t* bsel, uint32_t* row)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    int beg, end;
-    wave_range(N, w, beg, end);
-    uint32_t eq = 0;
-    for (int base = beg; base < end; base += kWave) {
-        const int i = base + lane;
-        eq += __popcll(__ballot(i < end && ki[i] == T));
-    }
-    uint32_t rank = wave_prefix(eq, row);
-    for (int base = beg; base < end; base += kWave) {
-        const int i = base + lane;
-        const bool act = i < end;
-        const uint32_t key = act ? ki[i] : 0xffffffffu;
-        const bool is_eq = act && key == T;
-        const uint64_t be = __ballot(is_eq);
-        const uint32_t r = rank + (uint32_t)__popcll(be & lanes_below(lane));
-        const bool take = act && (key < T || (is_eq && r < need));
-        const uint64_t bt = __ballot(take);
-        put_tile_bits(bimp, base, bt, lane);
-        put_tile_bits(bsel, base, bt, lane);
-        rank += (uint32_t)__popcll(be);
-    }
-}
-
-// Stage I marking by exact counting inside a bucket of at most kCountLimit
-// keys: keys below the bucket are kept, and a member is kept when fewer than
-// `need` members precede it in (key, index) order.  misc[8] must be 0.
-__device__ void stage1_mark_counted(const uint32_t* ki, int N, uint32_t prefix, uint32_t pmask,
-                                    uint32_t need, uint64_t* list, uint32_t* misc, uint32_t* bimp,
-                                    uint32_t* bsel)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    int beg, end;
-    wave_range(N, w, beg, end);
-    for (int base = beg; base < end; base += kWave) {
-        const int i = base + lane;
-        const bool act = i < end;
-        const uint32_t key = act ? ki[i] : 0u;
-        const uint64_t bt = __ballot(act && (key & pmask) < prefix);
-        put_tile_bits(bimp, base, bt, lane);
-        put_tile_bits(bsel, base, bt, lane);
-        append_member(act && (key & pmask) == prefix, key, i, list, &misc[8], lane);
-    }
-    __syncthreads();
-    keep_ranked_members(list, misc[8], need, bimp, bsel, nullptr, nullptr, nullptr);
-}
-
 // X^div positions in the ascending order of X^rem (R tokens, K2 picks).
 // Algorithm 1: 0, t, ..., (K2 - 1) t.  Real-interval variant (the interval
 // R / K2 of the method's prose): floor(j R / K2), j < K2.  Every product
@@ -590,555 +262,6 @@ struct Stride {
     }
     __device__ __forceinline__ uint32_t pos(uint32_t j) const { return real ? (j * R) / K2 : j * t; }
 };
-
-// Result of stage2_bucket.
-constexpr int kS2Failed = 0;   // nothing decided: sort instead
-constexpr int kS2Local = 1;    // every pick is in bsel
-constexpr int kS2Global = 2;   // this group's picks are in the global bitmap
-
-// Stage II by one bucketing pass and exact counting inside buckets.  Bucket
-// d of a remaining token is floor((s - s_min) * B / (s_max - s_min)) (B =
-// 1024 buckets over the remainder's key range: the image's whole range would
-// be cheaper to get, but Stage I tends to keep the tokens with outlying keys
-// and the rest would crowd into few buckets), a non-decreasing function of s
-// in fp32 (every step rounds monotonically), so bucket order agrees with key
-// order and counting inside a bucket the members smaller in (key, index)
-// order gives the exact rank.
-//   dgs   u16[n]  each token's bucket (kNoBucket outside X^rem), written by
-//                 the histogram pass, read by the list pass
-//   list  u16[n]  the indices of X^rem in bucket order; with `parts`
-//                 workgroups on a dense image each lists only the buckets it
-//                 ranks
-//   pairs         2 kWave words per wavefront for the dense ranking (may
-//                 overlap dgs, which is dead by then)
-//   comp  u64[n]  or null: for the per-token ranking, X^rem as
-//                 (key << 32 | index) in bucket order, listed instead of
-//                 `list` (one LDS read per compared member instead of two
-//                 dependent ones)
-// H (B words) must be zero.  Returns kS2Failed, having written only H, cur,
-// dgs, list and slot rows, when a bucket holds more than kBucketLimit tokens
-// or the key range is not finite.
-__device__ int stage2_bucket(const uint32_t* ks, const uint32_t* bimp, uint32_t* bsel, int N,
-                              int R, const Stride& sp, uint32_t* H, uint32_t* cur, uint16_t* list,
-                              uint16_t* dgs, uint32_t* pairs, uint32_t* row_lo, uint32_t* row_hi,
-                              uint32_t* row_a, uint32_t* row_b, int part, int parts,
-                              uint32_t* gpick, bool have_range, uint64_t* comp)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    int beg, end;
-    wave_range(N, w, beg, end);
-
-    // key range of X^rem (max of the complement gives the minimum), unless
-    // Stage I left it in the rows (the same decision in every thread)
-    if (!have_range) {
-        uint32_t nlo = 0, hi = 0;
-        for (int base = beg; base < end; base += kTileUnr * kWave) {
-            uint32_t k[kTileUnr];
-            bool rem[kTileUnr];
-            load_tiles(ks, base, end, lane, k);
-            rem_tiles(bimp, base, end, lane, rem);
-#pragma unroll
-            for (int u = 0; u < kTileUnr; ++u) {
-                if (rem[u]) {
-                    nlo = max(nlo, ~k[u]);
-                    hi = max(hi, k[u]);
-                }
-            }
-        }
-        nlo = wave_max_u32(nlo);
-        hi = wave_max_u32(hi);
-        if (lane == 0) {
-            row_lo[w] = nlo;
-            row_hi[w] = hi;
-        }
-        __syncthreads();
-    }
-    const uint32_t kmin = ~max_all(row_lo, lane), kmax = max_all(row_hi, lane);
-
-    if (kmin == kmax) {
-        // Every remaining key is equal: the stable order is the token order of X^rem.
-        uint32_t rc = 0;
-        for (int base = beg; base < end; base += kWave) {
-            const int i = base + lane;
-            rc += __popcll(__ballot(i < end && !bit_of(bimp, i)));
-        }
-        uint32_t r0 = wave_prefix(rc, row_a);
-        for (int base = beg; base < end; base += kWave) {
-            const int i = base + lane;
-            const bool rem = i < end && !bit_of(bimp, i);
-            const uint64_t br = __ballot(rem);
-            const uint32_t r = r0 + (uint32_t)__popcll(br & lanes_below(lane));
-            const uint64_t bp = __ballot(rem && sp.picks(r));
-            put_tile_union(bsel, bimp, base, bp, lane);
-            r0 += (uint32_t)__popcll(br);
-        }
-        return kS2Local;
-    }
-    const float fmin = key_value(kmin);
-    const float width = key_value(kmax) - fmin;
-    if (!(width > 0.f) || !(width < 3.0e38f)) return kS2Failed;   // not finite: sort instead
-    const float scale = (float)kBuckets / width;
-    if (!(scale < 3.0e38f)) return kS2Failed;   // a range of denormals: sort instead
-
-    for (int base = beg; base < end; base += kTileUnr * kWave) {
-        uint32_t k[kTileUnr];
-        bool rem[kTileUnr];
-        load_tiles(ks, base, end, lane, k);
-        rem_tiles(bimp, base, end, lane, rem);
-#pragma unroll
-        for (int u = 0; u < kTileUnr; ++u) {
-            const int i = base + u * kWave + lane;
-            const int dg = value_bucket(k[u], fmin, scale);
-            if (rem[u]) atomicAdd(&H[dg], 1u);
-            if (i < end) dgs[i] = rem[u] ? (uint16_t)dg : kNoBucket;
-        }
-    }
-    __syncthreads();
-    {   // exclusive bucket starts and the largest bucket; thread tid owns bucket tid
-        const uint32_t c = H[tid];
-        const uint32_t inc = wave_scan_add(c);
-        const uint32_t mx = wave_max_u32(c);
-        if (lane == kWave - 1) row_a[w] = inc;
-        if (lane == 0) row_b[w] = mx;
-        __syncthreads();
-        const uint32_t start = inc - c + sum_before(row_a, w, lane);
-        const uint32_t big = max_all(row_b, lane);
-        cur[tid] = start;
-        if (big > kBucketLimit) return kS2Failed;   // the same decision in every thread
-    }
-    __syncthreads();
-    // Dense ranking gives bucket q to wavefront q % (parts W) across the
-    // groups, so to group (q / W) % parts (parts is 1 or a power of two).
-    // The per-token ranking reads X^rem packed as (key, index) when the
-    // layout has room for it and buckets hold a member or more on average
-    // (packing costs a wider store per member; with fewer members per bucket
-    // there is little to compare: 576 tokens 0.56 -> 0.76 us of listing for
-    // no ranking gain; 2880 tokens 4.4 -> 3.3 us of ranking).
-    const bool dense = R >= kDenseRem;
-    const bool pack = !dense && comp != nullptr && R >= kBuckets;
-    auto list_pass = [&](auto packed) {   // one loop per form: the choice is per image
-        for (int base = beg; base < end; base += kTileUnr * kWave) {
-            uint32_t g[kTileUnr];
-            bool own[kTileUnr];
-#pragma unroll
-            for (int u = 0; u < kTileUnr; ++u) {
-                const int i = base + u * kWave + lane;
-                g[u] = i < end ? dgs[i] : kNoBucket;
-            }
-#pragma unroll
-            for (int u = 0; u < kTileUnr; ++u) {   // all cursor atomics, then the stores
-                own[u] = g[u] != kNoBucket && (!dense || ((g[u] / kW) & (parts - 1)) == (uint32_t)part);
-                if (own[u]) g[u] = atomicAdd(&cur[g[u]], 1u);
-            }
-#pragma unroll
-            for (int u = 0; u < kTileUnr; ++u) {
-                const int i = base + u * kWave + lane;
-                if constexpr (decltype(packed)::value) {
-                    if (own[u]) comp[g[u]] = ((uint64_t)ks[i] << 32) | (uint32_t)i;
-                } else {
-                    if (own[u]) list[g[u]] = (uint16_t)i;
-                }
-            }
-        }
-    };
-    if (pack) list_pass(std::true_type{});
-    else list_pass(std::false_type{});
-    __syncthreads();
-    if (dense) {
-        // Dense buckets: a wavefront ranks a whole bucket at a time, one
-        // member per lane (64 per chunk).  Each chunk of the bucket is
-        // staged as (index, key) word pairs in the wavefront's own `pairs`
-        // row, where every lane reads each pair with one broadcast LDS read
-        // and compares (key, index) as one 64-bit value.  LDS operations of
-        // one wavefront complete in order, so a pair written by any lane is
-        // visible to the reads after it.  With `parts` workgroups on the
-        // image, bucket q belongs to the wavefront numbered q % (parts W)
-        // across them (lane q / (parts W)); picks then go to the image's
-        // global pick bitmap gpick.
-        uint32_t* wp = pairs + 2 * kWave * w;
-        const int q = part * kW + w + parts * kW * lane;
-        const bool mine = q < kBuckets;
-        const uint32_t cnt = mine ? H[q] : 0u;
-        const uint32_t stop = mine ? cur[q] : 0u;
-        uint64_t todo = __ballot(cnt > 0);
-        while (todo) {
-            const int l = (int)__ffsll((long long)todo) - 1;
-            todo &= todo - 1;
-            const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)cnt, l);
-            const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)stop, l) - b;
-            for (uint32_t c0 = 0; c0 < b; c0 += kWave) {
-                const bool have = c0 + lane < b;
-                const uint32_t myid = have ? list[start + c0 + lane] : 0u;
-                const uint64_t me = have ? ((uint64_t)ks[myid] << 32) | myid : 0ull;
-                uint32_t r = 0;
-                for (uint32_t c1 = 0; c1 < b; c1 += kWave) {
-                    const bool oh = c1 + lane < b;
-                    const uint32_t oid = oh ? list[start + c1 + lane] : 0u;
-                    const uint32_t okey = oh ? ks[oid] : 0u;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    wp[2 * lane] = oid;
-                    wp[2 * lane + 1] = okey;
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    const uint32_t n1 = min((uint32_t)kWave, b - c1);
-                    uint32_t j = 0;
-                    for (; j + 4 <= n1; j += 4) {   // four reads in flight
-                        uint64_t o[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            o[u] = ((uint64_t)wp[2 * (j + u) + 1] << 32) | wp[2 * (j + u)];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) r += o[u] < me ? 1u : 0u;
-                    }
-                    for (; j < n1; ++j) {
-                        const uint64_t o = ((uint64_t)wp[2 * j + 1] << 32) | wp[2 * j];
-                        r += o < me ? 1u : 0u;
-                    }
-                }
-                const uint32_t rr = start + r;
-                if (have && sp.picks(rr)) {
-                    if (gpick) atomicOr(&gpick[myid >> 5], 1u << (myid & 31));
-                    else atomicOr(&bsel[myid >> 5], 1u << (myid & 31));
-                }
-            }
-        }
-        return gpick ? kS2Global : kS2Local;
-    }
-    for (int base = beg; base < end; base += kWave) {
-        const int i = base + lane;
-        const bool rem = i < end && !bit_of(bimp, i);
-        bool picked = false;
-        if (rem && pack) {
-            const uint32_t key = ks[i];
-            const uint64_t me = ((uint64_t)key << 32) | (uint32_t)i;
-            const int dg = value_bucket(key, fmin, scale);
-            const uint32_t stop = cur[dg];
-            uint32_t j = stop - H[dg];
-            uint32_t r = j;
-            for (; j + 8 <= stop; j += 8) {   // eight independent reads in flight
-                uint64_t c[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) c[u] = comp[j + u];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) r += c[u] < me ? 1u : 0u;
-            }
-            for (; j < stop; ++j) r += comp[j] < me ? 1u : 0u;
-            picked = sp.picks(r);
-        } else if (rem) {
-            const uint32_t key = ks[i];
-            const int dg = value_bucket(key, fmin, scale);
-            const uint32_t stop = cur[dg];
-            uint32_t j = stop - H[dg];
-            uint32_t r = j;
-            for (; j + 4 <= stop; j += 4) {
-                const uint32_t i0 = list[j], i1 = list[j + 1], i2 = list[j + 2], i3 = list[j + 3];
-                const uint32_t k0 = ks[i0], k1 = ks[i1], k2 = ks[i2], k3 = ks[i3];
-                r += (k0 < key || (k0 == key && i0 < (uint32_t)i)) ? 1u : 0u;
-                r += (k1 < key || (k1 == key && i1 < (uint32_t)i)) ? 1u : 0u;
-                r += (k2 < key || (k2 == key && i2 < (uint32_t)i)) ? 1u : 0u;
-                r += (k3 < key || (k3 == key && i3 < (uint32_t)i)) ? 1u : 0u;
-            }
-            for (; j < stop; ++j) {
-                const uint32_t ij = list[j], kj = ks[ij];
-                r += (kj < key || (kj == key && ij < (uint32_t)i)) ? 1u : 0u;
-            }
-            picked = sp.picks(r);
-        }
-        const uint64_t bp = __ballot(picked);
-        put_tile_union(bsel, bimp, base, bp, lane);
-    }
-    return kS2Local;
-}
-
-// Stage II by ordered compaction and a stable LSD radix sort of 16-bit
-// indices; sets the X^div bits in bsel.  idx_a / idx_b hold n u16 each.
-__device__ void stage2_radix(const uint32_t* ks, const uint32_t* bimp, uint32_t* bsel, int N, int K1,
-                             const Stride& sp, uint32_t VS, uint16_t* idx_a, uint16_t* idx_b,
-                             uint16_t* hist, uint32_t* row_c, uint32_t* row_s)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    int beg, end;
-    wave_range(N, w, beg, end);
-    uint32_t rc = 0;
-    for (int base = beg; base < end; base += kWave) {
-        const int i = base + lane;
-        rc += __popcll(__ballot(i < end && !bit_of(bimp, i)));
-    }
-    uint32_t pos = wave_prefix(rc, row_c);
-    for (int base = beg; base < end; base += kWave) {
-        const int i = base + lane;
-        const bool keep = i < end && !bit_of(bimp, i);
-        const uint64_t bk = __ballot(keep);
-        if (keep) idx_a[pos + __popcll(bk & lanes_below(lane))] = (uint16_t)i;
-        pos += (uint32_t)__popcll(bk);
-    }
-    const int R = N - K1;
-    int begR, endR;
-    wave_range(R, w, begR, endR);
-    uint16_t* src = idx_a;
-    uint16_t* dst = idx_b;
-    for (int shift = 0; shift < 32; shift += 8) {
-        if (((VS >> shift) & 255u) == 0) continue;   // every key has the same byte here
-        uint32_t* h32 = reinterpret_cast<uint32_t*>(hist);
-        for (int i = tid; i < 128 * kW; i += kThreads) h32[i] = 0;
-        __syncthreads();
-        for (int base = begR; base < endR; base += kWave) {
-            const int i = base + lane;
-            const bool act = i < endR;
-            const uint32_t id = act ? src[i] : 0u;
-            const uint32_t dg = act ? (ks[id] >> shift) & 255u : 0u;
-            const uint64_t m = same_digit(dg, act);
-            if (act && is_leader(m, lane)) hist[dg * kW + w] = (uint16_t)(hist[dg * kW + w] + __popcll(m));
-        }
-        __syncthreads();
-        {   // exclusive scan of hist in (digit, wavefront) order, 4 entries per thread
-            const int e = tid * 4;
-            const uint2 hv = *reinterpret_cast<const uint2*>(hist + e);
-            const uint32_t h0 = hv.x & 0xffffu, h1 = hv.x >> 16, h2 = hv.y & 0xffffu, h3 = hv.y >> 16;
-            const uint32_t v = h0 + h1 + h2 + h3;
-            const uint32_t inc = wave_scan_add(v);
-            if (lane == kWave - 1) row_s[w] = inc;
-            __syncthreads();
-            const uint32_t b0 = inc - v + sum_before(row_s, w, lane);
-            const uint32_t o1 = b0 + h0, o2 = o1 + h1, o3 = o2 + h2;
-            *reinterpret_cast<uint2*>(hist + e) = make_uint2(b0 | (o1 << 16), o2 | (o3 << 16));
-        }
-        __syncthreads();
-        for (int base = begR; base < endR; base += kWave) {
-            const int i = base + lane;
-            const bool act = i < endR;
-            const uint32_t id = act ? src[i] : 0u;
-            const uint32_t dg = act ? (ks[id] >> shift) & 255u : 0u;
-            const uint64_t m = same_digit(dg, act);
-            const uint32_t off = act ? hist[dg * kW + w] : 0u;
-            if (act) dst[off + __popcll(m & lanes_below(lane))] = (uint16_t)id;
-            if (act && is_leader(m, lane)) hist[dg * kW + w] = (uint16_t)(off + __popcll(m));
-        }
-        __syncthreads();
-        uint16_t* tmp = src;
-        src = dst;
-        dst = tmp;
-    }
-    __syncthreads();   // the compaction (or the last pass) is visible to every picker
-    for (int j = tid; j < (int)sp.K2; j += kThreads) {
-        const int id = src[sp.pos((uint32_t)j)];
-        atomicOr(&bsel[id >> 5], 1u << (id & 31));
-    }
-}
-
-// Lane t's value of a 64-bit register, on every lane (t wavefront-uniform).
-__device__ __forceinline__ uint64_t lane_u64(uint64_t v, int t)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, t);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), t);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// X* in ascending token index: out_idx (image-local), out_src, out_rows.
-// Lane t of each wavefront holds the 64-bit bsel and bimp words of the
-// wavefront's t-th tile (a range has at most 64 tiles at the capacity's N),
-// so the counts and the ordered writes read LDS once per wavefront.
-__device__ void emit(const SelectArgs& a, const Img& d, const uint32_t* bimp, const uint32_t* bsel,
-                     uint32_t* row)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    int beg, end;
-    wave_range(d.n, w, beg, end);
-    const int tiles = (end - beg + kWave - 1) / kWave;
-    uint64_t sel = 0, imp = 0;
-    if (lane < tiles) {
-        sel = *reinterpret_cast<const uint64_t*>(bsel + ((beg >> 5) + 2 * lane));
-        imp = *reinterpret_cast<const uint64_t*>(bimp + ((beg >> 5) + 2 * lane));
-        const int valid = end - (beg + kWave * lane);   // tokens of this tile inside the image
-        if (valid < kWave) sel &= (1ull << valid) - 1ull;
-    }
-    uint32_t opos = wave_prefix(wave_sum_u32((uint32_t)__popcll(sel)), row);
-    const int K = d.k1 + d.k2;
-    for (int t = 0; t < tiles; ++t) {
-        const uint64_t m = lane_u64(sel, t), im = lane_u64(imp, t);
-        const int i = beg + kWave * t + lane;
-        const int slot = (int)opos + __popcll(m & lanes_below(lane));
-        if (((m >> lane) & 1ull) && slot < K) {   // never more than K writes, whatever the keys
-            const int o = d.out_off + slot;
-            a.out_idx[o] = i;
-            if (a.out_src) a.out_src[o] = ((im >> lane) & 1ull) ? 0 : 1;
-            if (a.out_rows) a.out_rows[o] = d.row_off + i;
-        }
-        opos += (uint32_t)__popcll(m);
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int G = a.groups > 0 ? a.groups : 1;
-    const int local = (int)blockIdx.x / G, part = (int)blockIdx.x % G;
-    const int img = a.img0 + local;
-    const Img d = image_of(a, local);
-    const int N = d.n, K1 = d.k1, K2 = d.k2;
-    // A large image is shared by G workgroups: each repeats the deterministic
-    // Stage I and bucketing in its own LDS and ranks 1/G of the buckets into
-    // the image's global pick bitmap; emit_kernel then writes the output.
-    const bool split = G > 1 && K2 > 0 && N - K1 >= kDenseRem;   // as select_shares
-    if (part > 0 && !split) return;
-    const LdsLayout L = lds_layout(N);
-    uint32_t* ks = reinterpret_cast<uint32_t*>(smem + L.ks);
-    uint32_t* ki = reinterpret_cast<uint32_t*>(smem + L.ki);
-    uint32_t* bimp = reinterpret_cast<uint32_t*>(smem + L.bimp);
-    uint32_t* bsel = reinterpret_cast<uint32_t*>(smem + L.bsel);
-    uint32_t* area = reinterpret_cast<uint32_t*>(smem + L.area);
-    uint32_t* slots = reinterpret_cast<uint32_t*>(smem + L.slots);
-    uint32_t* misc = reinterpret_cast<uint32_t*>(smem + L.misc);
-    const int nw = 2 * ((N + 63) / 64);
-
-    // Slot rows (each written, then read after a barrier, then not touched
-    // again until further barriers have passed): 0-3 key ranges and varying
-    // bits, 4 Stage I scans, 5 Stage I tie ranks, 6-7 Stage II ranges (from
-    // Stage I's bucket path or Stage II's own pass), 2-3 Stage II scans, 4-5
-    // the radix sort, 6 the output offsets.
-    if (threadIdx.x < 16) misc[threadIdx.x] = 0;
-    const KeyStats ksd = load_keys(a, d, ki, ks, area, kBuckets, slots);
-    const uint32_t kimin = ksd.kimin, kimax = ksd.kimax;
-
-    // ---- Stage I ---------------------------------------------------------------
-    uint64_t* list1 = reinterpret_cast<uint64_t*>(area + kBuckets);   // kCountLimit u64
-    bool s2_range = false;   // Stage I's bucket path leaves X^rem's key range in rows 6-7
-    if (K1 == 0 || K1 == N) {
-        const uint32_t fill = K1 ? 0xffffffffu : 0u;
-        for (int i = threadIdx.x; i < nw; i += kThreads) {
-            bimp[i] = fill;
-            bsel[i] = fill;
-        }
-    } else if (kimin == kimax) {   // every key is equal: the first K1 tokens
-        stage1_mark_resolved(ki, N, kimin, (uint32_t)K1, bimp, bsel, slots + 5 * kW);
-    } else if (stage1_bucket(ki, ks, N, (uint32_t)K1, kimin, kimax, area, list1, misc, slots + 4 * kW,
-                             slots + 6 * kW, slots + 7 * kW, bimp, bsel)) {
-        s2_range = true;
-    } else {
-        __syncthreads();   // everyone is past the bucket attempt: reset its scratch
-        area[threadIdx.x] = 0;
-        if (threadIdx.x < 16) misc[threadIdx.x] = 0;
-        __syncthreads();
-        uint32_t prefix = ksd.k0i & ~ksd.VI, pmask = ~ksd.VI, need = (uint32_t)K1, m = (uint32_t)N;
-        bool resolved;
-        stage1_narrow(ki, N, ksd.VI, area, misc, kCountLimit, prefix, pmask, need, m, resolved);
-        if (resolved) stage1_mark_resolved(ki, N, prefix, need, bimp, bsel, slots + 5 * kW);
-        else stage1_mark_counted(ki, N, prefix, pmask, need, list1, misc, bimp, bsel);
-    }
-    __syncthreads();   // Stage I's histograms and list are read no more; ki is dead
-    area[threadIdx.x] = 0;   // Stage II bucket counts
-    __syncthreads();
-
-    // ---- Stage II --------------------------------------------------------------
-    if (K2 > 0) {
-        uint16_t* idx = reinterpret_cast<uint16_t*>(ki);
-        const size_t wbase = (size_t)(d.row_off >> 5) + 2 * (size_t)img;
-        uint32_t* gpick = split ? a.gsel + wbase : nullptr;
-        const Stride sp{(uint32_t)d.t, (uint32_t)(N - K1), (uint32_t)K2, a.stride_real != 0};
-        // ki's bytes after Stage I: the u16 list of X^rem in the lower half;
-        // the u16 bucket index of every token in the upper half (until the
-        // list is built); then the dense ranking's pairs above the list, with
-        // room for 2 kWave words per wavefront once N >= kDenseRem.
-        int st = stage2_bucket(ks, bimp, bsel, N, N - K1, sp, area, area + kBuckets, idx, idx + N,
-                               ki + (N + 1) / 2, slots + 6 * kW, slots + 7 * kW, slots + 2 * kW,
-                               slots + 3 * kW, split ? part : 0, split ? G : 1, gpick, s2_range,
-                               L.has_comp ? reinterpret_cast<uint64_t*>(smem + L.comp) : nullptr);
-        if (st == kS2Failed) {
-            if (part > 0) return;   // the same decision in every group: group 0 sorts
-            __syncthreads();        // every thread is past the bucket attempt
-            stage2_radix(ks, bimp, bsel, N, K1, sp, ksd.VS, idx, idx + N,
-                         reinterpret_cast<uint16_t*>(area), slots + 4 * kW, slots + 5 * kW);
-            st = kS2Local;
-        }
-        if (split) {
-            // The output of a shared image is written by emit_kernel after this
-            // launch: group 0 publishes X^imp (and picks it made alone).
-            if (part == 0) {
-                __syncthreads();
-                for (int i = threadIdx.x; i < (N + 31) / 32; i += kThreads) {
-                    a.gimp[wbase + i] = bimp[i];
-                    if (st == kS2Local) {
-                        const uint32_t extra = bsel[i] & ~bimp[i];
-                        if (extra) atomicOr(&gpick[i], extra);
-                    }
-                }
-            }
-            return;
-        }
-    }
-    __syncthreads();
-    emit(a, d, bimp, bsel, slots + 6 * kW);
-}
-
-// Output of the images select_kernel shared between workgroups: X^imp and the
-// picks from the global bitmaps (which are cleared for the next call), then
-// the ordered output.  One workgroup per image of the launch.
-__global__ __launch_bounds__(kThreads) void emit_kernel(SelectArgs a)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int G = a.groups > 0 ? a.groups : 1;
-    const int local = (int)blockIdx.x;
-    const int img = a.img0 + local;
-    const Img d = image_of(a, local);
-    const int N = d.n, K1 = d.k1, K2 = d.k2;
-    if (!(G > 1 && K2 > 0 && N - K1 >= kDenseRem)) return;   // emitted by select_kernel
-    const int nw = 2 * ((N + 63) / 64);
-    uint32_t* bimp = reinterpret_cast<uint32_t*>(smem);
-    uint32_t* bsel = bimp + nw;
-    uint32_t* slots = bsel + nw;
-    const size_t wbase = (size_t)(d.row_off >> 5) + 2 * (size_t)img;
-    for (int i = threadIdx.x; i < (N + 31) / 32; i += kThreads) {
-        const uint32_t im = a.gimp[wbase + i];
-        bimp[i] = im;
-        bsel[i] = im | a.gsel[wbase + i];
-        a.gsel[wbase + i] = 0u;
-    }
-    __syncthreads();
-    emit(a, d, bimp, bsel, slots);
-}
-
-// ---- images of at most kSmallSelectN tokens: one token per thread ------------
-//
-// Both stages are ranked in the same passes.  Every token gets its exact rank
-// in (Stage II key, index) order among all N tokens, and its place relative
-// to K1 in (Stage I key, index) order (counted exactly only inside the bucket
-// that holds the K1 boundary); X^imp is the places below K1, and a token of X^rem ranks in X^rem as
-// its Stage II rank minus the X^imp tokens ranked below it (read from a
-// bitmap of X^imp in Stage II rank order), which decides the stride picks.
-// Ranks come from value buckets and exact counting inside a bucket: bucket =
-// clamp(floor((v - lo) nb / (hi - lo)), 0, nb - 1) is non-decreasing in the
-// key, so rank = (tokens in lower buckets) + (members of the token's bucket
-// smaller in (key, index) order).  lo and hi are about the 1.5 % and 98.5 %
-// quantiles of a 64-key sample, so outliers (all-zero rows, zero-norm states)
-// land in the two end buckets instead of crowding the bulk into a few; when
-// the sample's range is not a finite positive float width, buckets are equal
-// ranges of the order-preserving key itself.  All keys equal: rank = index.
-// Phases are separated by eight workgroup barriers.  With a fused gather, G
-// workgroups share an image: each repeats the selection and copies every G-th
-// share of the kept rows (group 0 writes out_idx / out_src / out_rows).
-
-struct SmallLayout {
-    size_t hi, hs, si, ss, li, ls, samp, slots, misc, imps, kept, total;
-};
-
-__host__ __device__ inline SmallLayout small_layout(int T)
-{
-    SmallLayout L;
-    size_t o = 0;
-    L.hi = o;  o += 4 * (size_t)T;            // Stage I histogram, then cursors
-    L.hs = o;  o += 4 * (size_t)T;            // Stage II histogram, then cursors
-    L.si = o;  o += 4 * ((size_t)T + 1);      // Stage I bucket starts
-    L.ss = o;  o += 4 * ((size_t)T + 1);      // Stage II bucket starts
-    o = align_up(o, 16);
-    L.li = o;  o += 8 * (size_t)T;            // (key << 32 | index) in Stage I bucket order
-    L.ls = o;  o += 8 * (size_t)T;            // the same for Stage II
-    L.samp = o; o += 8 * 128;                 // 64-key samples of both keys, (key << 6 | k)
-    L.slots = o; o += 4 * 8 * kW;             // per-wavefront partial values
-    L.misc = o; o += 4 * 16;                  // broadcast slots
-    L.imps = o; o += 4 * 32;                  // X^imp bitmap in Stage II rank order
-    L.kept = o; o += 4 * (size_t)T;           // token of each output slot (fused gather)
-    L.total = o;
-    return L;
-}
 
 // Bucketing of one key over [lo, hi] (order keys) into nb buckets.
 struct Bucketing {
@@ -1190,17 +313,23 @@ __device__ __forceinline__ int bucket_of(const Bucketing& b, uint32_t k, int nb)
     return 0;
 }
 
-// About the 1.5 % and 98.5 % quantiles of 64 sampled keys of an image (all
-// of them for N <= 64), computed by one wavefront without the workgroup:
+// The keys of ranks lo_rank and hi_rank among 64 sampled keys of an image (all
+// of them for N <= 64; a rank outside [0, 64) publishes nothing), by one
+// wavefront without the workgroup:
 // lane k loads sample k (token floor(k N / 64)), the wave stages the samples
 // as distinct (key << 6 | k) values in its own LDS row, every lane ranks its
 // sample among the 64 (two per 16-byte broadcast read), and the lanes holding
 // ranks lo_rank and hi_rank publish their keys in out[0], out[1].
-__device__ __forceinline__ void sample_quantiles(const float* keys, int N, int lane, uint64_t* samp,
+__device__ __forceinline__ int sample_index(int N, int lane)
+{
+    return N > kWave ? (int)(((int64_t)lane * N) >> 6) : lane;
+}
+
+template <int Q = 16>   // pairs of samples in flight
+__device__ __forceinline__ void sample_quantiles(uint32_t key, int lane, uint64_t* samp, int lo_rank, int hi_rank,
                                                  uint32_t* out)
 {
-    const int st = N > kWave ? (int)(((int64_t)lane * N) >> 6) : lane;
-    const uint64_t mine = ((uint64_t)(st < N ? order_key(keys[st]) : 0xffffffffu) << 6) | (uint64_t)lane;
+    const uint64_t mine = ((uint64_t)key << 6) | (uint64_t)lane;
     samp[lane] = mine;
     // LDS operations of one wavefront complete in order: the row written
     // above is visible to the reads below
@@ -1209,14 +338,13 @@ __device__ __forceinline__ void sample_quantiles(const float* keys, int N, int l
     const ulonglong2* sv = reinterpret_cast<const ulonglong2*>(samp);
     int r = 0;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        ulonglong2 q[16];
+    for (int h = 0; h < 32 / Q; ++h) {
+        ulonglong2 q[Q];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) q[j] = sv[16 * h + j];
+        for (int j = 0; j < Q; ++j) q[j] = sv[Q * h + j];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) r += (q[j].x < mine ? 1 : 0) + (q[j].y < mine ? 1 : 0);
+        for (int j = 0; j < Q; ++j) r += (q[j].x < mine ? 1 : 0) + (q[j].y < mine ? 1 : 0);
     }
-    const int lo_rank = N > kWave ? 1 : 0, hi_rank = N > kWave ? kWave - 2 : N - 1;
     if (r == lo_rank) out[0] = (uint32_t)(mine >> 6);
     if (r == hi_rank) out[1] = (uint32_t)(mine >> 6);
 }
@@ -1233,6 +361,696 @@ __device__ __forceinline__ uint32_t rank_in(const uint64_t* list, uint32_t beg, 
     }
     for (; j < end; ++j) r += list[j] < me ? 1u : 0u;
     return r;
+}
+
+// Lane t's value of a 64-bit register, on every lane (t wavefront-uniform).
+__device__ __forceinline__ uint64_t lane_u64(uint64_t v, int t)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, t);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), t);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// The tokens not in `skip` (R of them) in (key, index) order: ordered compaction,
+// then a stable LSD radix sort of 16-bit indices over the bytes that `vary`
+// says can differ.  Returns the sorted list, one of idx_a / idx_b (n u16
+// each); the workgroup is past a barrier.
+__device__ __forceinline__ const uint16_t* radix_sort(const uint32_t* ks, const uint32_t* skip, int N, int R, uint32_t vary,
+                                      uint16_t* idx_a, uint16_t* idx_b, uint16_t* hist, uint32_t* row_c,
+                                      uint32_t* row_s)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    int beg, end;
+    wave_range(N, w, beg, end);
+    uint32_t rc = 0;
+    for (int base = beg; base < end; base += kWave) {
+        const int i = base + lane;
+        rc += __popcll(__ballot(i < end && !bit_of(skip, i)));
+    }
+    uint32_t pos = wave_prefix(rc, row_c);
+    for (int base = beg; base < end; base += kWave) {
+        const int i = base + lane;
+        const bool keep = i < end && !bit_of(skip, i);
+        const uint64_t bk = __ballot(keep);
+        if (keep) idx_a[pos + __popcll(bk & lanes_below(lane))] = (uint16_t)i;
+        pos += (uint32_t)__popcll(bk);
+    }
+    int begR, endR;
+    wave_range(R, w, begR, endR);
+    uint16_t* src = idx_a;
+    uint16_t* dst = idx_b;
+    for (int shift = 0; shift < 32; shift += 8) {
+        if (((vary >> shift) & 255u) == 0) continue;   // every key has the same byte here
+        uint32_t* h32 = reinterpret_cast<uint32_t*>(hist);
+        for (int i = tid; i < 128 * kW; i += kThreads) h32[i] = 0;
+        __syncthreads();
+        for (int base = begR; base < endR; base += kWave) {
+            const int i = base + lane;
+            const bool act = i < endR;
+            const uint32_t id = act ? src[i] : 0u;
+            const uint32_t dg = act ? (ks[id] >> shift) & 255u : 0u;
+            const uint64_t m = same_digit(dg, act);
+            if (act && is_leader(m, lane)) hist[dg * kW + w] = (uint16_t)(hist[dg * kW + w] + __popcll(m));
+        }
+        __syncthreads();
+        {   // exclusive scan of hist in (digit, wavefront) order, 4 entries per thread
+            const int e = tid * 4;
+            const uint2 hv = *reinterpret_cast<const uint2*>(hist + e);
+            const uint32_t h0 = hv.x & 0xffffu, h1 = hv.x >> 16, h2 = hv.y & 0xffffu, h3 = hv.y >> 16;
+            const uint32_t v = h0 + h1 + h2 + h3;
+            const uint32_t inc = wave_scan_add(v);
+            if (lane == kWave - 1) row_s[w] = inc;
+            __syncthreads();
+            const uint32_t b0 = inc - v + sum_before(row_s, w, lane);
+            const uint32_t o1 = b0 + h0, o2 = o1 + h1, o3 = o2 + h2;
+            *reinterpret_cast<uint2*>(hist + e) = make_uint2(b0 | (o1 << 16), o2 | (o3 << 16));
+        }
+        __syncthreads();
+        for (int base = begR; base < endR; base += kWave) {
+            const int i = base + lane;
+            const bool act = i < endR;
+            const uint32_t id = act ? src[i] : 0u;
+            const uint32_t dg = act ? (ks[id] >> shift) & 255u : 0u;
+            const uint64_t m = same_digit(dg, act);
+            const uint32_t off = act ? hist[dg * kW + w] : 0u;
+            if (act) dst[off + __popcll(m & lanes_below(lane))] = (uint16_t)id;
+            if (act && is_leader(m, lane)) hist[dg * kW + w] = (uint16_t)(off + __popcll(m));
+        }
+        __syncthreads();
+        uint16_t* tmp = src;
+        src = dst;
+        dst = tmp;
+    }
+    __syncthreads();   // the compaction (or the last pass) is visible to every reader
+    return src;
+}
+
+// Word of an image's bitmaps at which this lane's tile of the output step starts,
+// or -1 for a lane without a tile.
+__device__ __forceinline__ int tile_word(int n)
+{
+    int beg, end;
+    wave_range(n, (int)threadIdx.x / kWave, beg, end);
+    const int at = beg + kWave * ((int)threadIdx.x & (kWave - 1));
+    return at < end ? at >> 5 : -1;
+}
+
+// X* in ascending token index: out_idx (image-local), out_src, out_rows.
+// Lane t of each wavefront holds the 64-bit words of X* (sel) and X^imp (imp) of
+// the wavefront's t-th tile (a range has at most 64 tiles at the capacity's N;
+// tile_word says where a lane's words start).
+__device__ __forceinline__ void emit(const SelectArgs& a, const Img& d, uint64_t sel, uint64_t imp, uint32_t* row)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    int beg, end;
+    wave_range(d.n, w, beg, end);
+    const int tiles = (end - beg + kWave - 1) / kWave;
+    const int valid = end - (beg + kWave * lane);   // tokens of this lane's tile inside the image
+    if (valid < kWave) sel &= valid > 0 ? (1ull << valid) - 1ull : 0ull;
+    uint32_t opos = wave_prefix(wave_sum_u32((uint32_t)__popcll(sel)), row);
+    const int K = d.k1 + d.k2;
+    for (int t = 0; t < tiles; ++t) {
+        const uint64_t m = lane_u64(sel, t), im = lane_u64(imp, t);
+        const int i = beg + kWave * t + lane;
+        const int slot = (int)opos + __popcll(m & lanes_below(lane));
+        if (((m >> lane) & 1ull) && slot < K) {   // never more than K writes, whatever the keys
+            const int o = d.out_off + slot;
+            a.out_idx[o] = i;
+            if (a.out_src) a.out_src[o] = ((im >> lane) & 1ull) ? 0 : 1;
+            if (a.out_rows) a.out_rows[o] = d.row_off + i;
+        }
+        opos += (uint32_t)__popcll(m);
+    }
+}
+
+// One pass over the image: f(tokens of this thread) for kUnr tokens at a time,
+// i[v] = (u + v) kThreads + threadIdx.x, slot u + v.  Whole wavefronts take
+// part; indices beyond the image come too (f masks them), their reads clamped.
+template <typename F>
+__device__ __forceinline__ void for_tokens(int N, F f)
+{
+    for (int u = 0; u * kThreads < N; u += kUnr) f(u, u * kThreads + (int)threadIdx.x);
+}
+
+__device__ __forceinline__ void read_keys(const uint32_t* v, int i0, int N, uint32_t (&out)[kUnr])
+{
+#pragma unroll
+    for (int q = 0; q < kUnr; ++q) out[q] = v[min(i0 + q * kThreads, N - 1)];
+}
+
+// A barrier for what is exchanged through LDS: loads from memory stay in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Append (key, index) of the lanes of `bm` (not empty) to `list`, reserving the
+// wavefront's slots with one atomic on the counter `cnt`.
+__device__ __forceinline__ void append_member(uint64_t bm, uint32_t key, int i, uint64_t* list, uint32_t* cnt,
+                                              int lane)
+{
+    uint32_t b0 = 0;
+    if (lane == 0) b0 = atomicAdd(cnt, (uint32_t)__popcll(bm));
+    b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
+    const uint32_t at = b0 + (uint32_t)__popcll(bm & lanes_below(lane));
+    if ((bm >> lane & 1ull) && at < kMembers) list[at] = pair_of(key, (uint32_t)i);   // never beyond, whatever the keys
+}
+
+// The scan after one histogram of Stage I: thread t owns bucket t of H (zero on
+// return); below / inside: the tokens below the range / in it.  The bucket that
+// holds the K1-th smallest goes to misc[kMRound ..].
+__device__ __forceinline__ void stage1_scan(uint32_t wave_below, uint32_t K1, uint32_t* H, uint32_t* misc,
+                                            uint32_t* row_b, uint32_t* row_c, uint32_t& below, uint32_t& inside)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    if (lane == 0) row_b[w] = wave_below;
+    __syncthreads();
+    const uint32_t c = H[tid];
+    H[tid] = 0u;
+    const uint32_t inc = wave_scan_add(c);
+    if (lane == kWave - 1) row_c[w] = inc;
+    __syncthreads();
+    below = sum_before(row_b, kW, lane);
+    inside = sum_before(row_c, kW, lane);
+    const uint32_t start = below + inc - c + sum_before(row_c, w, lane);
+    if (start < K1 && K1 <= start + c) {
+        misc[kMRound] = (uint32_t)tid;
+        misc[kMRound + 1] = K1 - start;
+        misc[kMRound + 2] = c;
+    }
+    __syncthreads();
+}
+
+// One round's histogram over the keys in LDS: tokens with lo <= v <= hi go to
+// bucket (v - lo) >> sh, those below lo are counted for the wavefront.  v is
+// the key, or (INDEX) the index of the tokens whose key is `only`.
+template <bool INDEX>
+__device__ uint32_t stage1_histogram(const uint32_t* ki, int N, uint32_t only, uint32_t lo, uint32_t hi, int sh,
+                                     uint32_t* H)
+{
+    uint32_t nb = 0;
+    for_tokens(N, [&](int, int i0) {
+        uint32_t k[kUnr];
+        read_keys(ki, i0, N, k);
+#pragma unroll
+        for (int q = 0; q < kUnr; ++q) {
+            const int i = i0 + q * kThreads;
+            const uint32_t v = INDEX ? (uint32_t)i : k[q];
+            const bool have = i < N && (!INDEX || k[q] == only);
+            nb += (uint32_t)__popcll(__ballot(have && v < lo));
+            if (have && v - lo <= hi - lo) atomicAdd(&H[(v - lo) >> sh], 1u);
+        }
+    });
+    return nb;
+}
+
+// Bits to drop so that the range [lo, hi] fits the buckets.
+__device__ __forceinline__ int range_shift(uint32_t lo, uint32_t hi)
+{
+    const int bits = hi > lo ? 32 - __clz((int)(hi - lo)) : 0;
+    static_assert(kBuckets == 1 << 10, "ten bits of a range");
+    return bits > 10 ? bits - 10 : 0;
+}
+
+// The tokens that hold T: (lo, ilo) <= (key, index) <= (hi, ihi), at most
+// kMembers of them, T the need-th smallest.
+struct Boundary {
+    uint32_t lo, hi, ilo, ihi, need;
+    bool tie;   // one key value, narrowed by index
+};
+
+// From the first range's scan on.
+__device__ __forceinline__ Boundary stage1_boundary(const uint32_t* ki, int N, uint32_t K1, uint32_t lo, uint32_t hi,
+                                                    uint32_t below, uint32_t inside, uint32_t* H, uint32_t* misc,
+                                                    uint32_t* row_b, uint32_t* row_c)
+{
+    Boundary r;
+    uint32_t m;
+    for (;;) {
+        if (K1 <= below) {   // the sampled range lies above T
+            hi = lo - 1;
+            lo = 0u;
+        } else if (K1 > below + inside) {   // or below it
+            lo = hi + 1;
+            hi = 0xffffffffu;
+        } else {
+            const int sh = range_shift(lo, hi);
+            r.need = misc[kMRound + 1];
+            m = misc[kMRound + 2];
+            lo += misc[kMRound] << sh;
+            hi = min(hi - lo, (1u << sh) - 1u) + lo;
+            if (m <= kMembers || sh == 0) break;
+        }
+        const uint32_t nb = stage1_histogram<false>(ki, N, 0u, lo, hi, range_shift(lo, hi), H);
+        stage1_scan(nb, K1, H, misc, row_b, row_c, below, inside);
+    }
+    r.lo = lo;
+    r.hi = hi;
+    r.ilo = 0u;
+    r.ihi = 0xffffffffu;
+    r.tie = m > kMembers;
+    if (r.tie) {   // tokens of one key value: those of the lowest indices
+        constexpr int kIdxShift = 5;
+        static_assert(kMaxSlots * kThreads <= kBuckets << kIdxShift, "every index has a bucket");
+        const uint32_t nb = stage1_histogram<true>(ki, N, lo, 0u, (uint32_t)N - 1u, kIdxShift, H);
+        stage1_scan(nb, r.need, H, misc, row_b, row_c, below, inside);
+        r.need = misc[kMRound + 1];
+        r.ilo = misc[kMRound] << kIdxShift;
+        r.ihi = r.ilo + ((1u << kIdxShift) - 1u);
+    }
+    return r;
+}
+
+// What the second pass needs of the workgroup's share of X^rem.
+struct Share {
+    uint64_t lo, hi;   // first pair owned, first pair not owned any more
+    bool open;         // no upper end
+};
+
+// The second pass: X^imp bits (bimp, and bsel if given; null: none), the
+// boundary's members, the own tokens (bit u of `own`: slot u) and the count
+// of X^rem below them for the wavefront.  EXACT compares (key, index); without
+// it the boundary and the share are ranges of keys.  The counts come from
+// ballots of single comparisons, combined as scalars: a ballot of a combined
+// condition costs two vector instructions more, and a tile has about ten.
+template <bool EXACT, bool FULL>   // FULL: every token read is one of the image
+__device__ __forceinline__ void second_pass_step(const uint32_t* ki, const uint32_t* ks, int N, int u, const Boundary& bd,
+                                                 uint64_t imp_end, bool members_left, const Share& sh,
+                                                 uint64_t* members, uint32_t* count, uint32_t* bimp, uint32_t* bsel,
+                                                 uint32_t& own, uint32_t& rem_below)
+{
+    const int lane = threadIdx.x & (kWave - 1), i0 = u * kThreads + (int)threadIdx.x;
+    const uint64_t mhi = pair_of(bd.hi, bd.ihi);
+    const uint32_t klo = (uint32_t)(sh.lo >> 32), khi = sh.open ? 0xffffffffu : (uint32_t)(sh.hi >> 32) - 1u;
+    uint32_t qi[kUnr], qs[kUnr];
+    if constexpr (FULL) {
+#pragma unroll
+        for (int q = 0; q < kUnr; ++q) {
+            qi[q] = ki[i0 + q * kThreads];
+            qs[q] = ks[i0 + q * kThreads];
+        }
+    } else {
+        read_keys(ki, i0, N, qi);
+        read_keys(ks, i0, N, qs);
+    }
+#pragma unroll
+    for (int q = 0; q < kUnr; ++q) {
+        const int i = i0 + q * kThreads, tb = i - lane;
+        const bool valid = FULL || i < N;
+        const uint64_t pi = pair_of(qi[q], (uint32_t)i), ps = pair_of(qs[q], (uint32_t)i);
+        const bool imp = EXACT ? pi < imp_end : qi[q] < bd.lo;
+        const bool upto = EXACT ? pi <= mhi : qi[q] <= bd.hi;   // X^imp or a member
+        const bool below = EXACT ? ps < sh.lo : qs[q] < klo;
+        const bool under = EXACT ? sh.open || ps < sh.hi : qs[q] <= khi;
+        const uint64_t vm = FULL ? ~0ull : __ballot(valid);
+        const uint64_t mi = __ballot(imp) & vm;
+        const uint64_t mm = EXACT && !members_left ? 0ull : __ballot(upto) & vm & ~mi;
+        rem_below += (uint32_t)__popcll(__ballot(below) & vm & ~(mi | mm));
+        if (mm) append_member(mm, qi[q], i, members, count, lane);
+        if (bimp && (FULL || tb < N)) {
+            put_tile_bits(bimp, tb, mi, lane);
+            if (bsel) put_tile_bits(bsel, tb, mi, lane);
+        }
+        const bool rem = valid && !(EXACT ? imp || (members_left && upto) : upto);   // imp implies upto
+        own |= rem && !below && under ? 1u << (u + q) : 0u;
+    }
+}
+
+template <bool EXACT>
+__device__ __forceinline__ void second_pass(const uint32_t* ki, const uint32_t* ks, int N, const Boundary& bd,
+                                            uint64_t imp_end, bool members_left, const Share& sh, uint64_t* members,
+                                            uint32_t* count, uint32_t* bimp, uint32_t* bsel, uint32_t& own,
+                                            uint32_t& rem_below)
+{
+    int u = 0;
+    if constexpr (!EXACT)
+        for (; (u + kUnr) * kThreads <= N; u += kUnr)
+            second_pass_step<false, true>(ki, ks, N, u, bd, imp_end, members_left, sh, members, count, bimp,
+                                                bsel, own, rem_below);
+    for (; u * kThreads < N; u += kUnr)
+        second_pass_step<EXACT, false>(ki, ks, N, u, bd, imp_end, members_left, sh, members, count, bimp, bsel,
+                                             own, rem_below);
+}
+
+// A place in [0, n), n < 65536, that differs from k to k.
+__device__ __forceinline__ uint32_t scatter(int k, uint32_t n)
+{
+    return (((uint32_t)k * 2654435761u) >> 16) * n >> 16;
+}
+
+// Sample k of a shared image: one token of the k-th of kSample equal parts,
+// at a place that differs from part to part, so that a period in the tokens
+// (frames of a clip) does not meet a period in the samples.
+__device__ __forceinline__ int sample_token(int k, int N)
+{
+    return (int)((uint32_t)k * (uint32_t)N / kSample + scatter(k, (uint32_t)N / kSample));
+}
+
+// The keys are loaded in one burst, S of each kind a thread (N <= S kThreads);
+// the samples, loaded before them, are ranked while they arrive.
+// S is 4, 10 or 19 by the launch's largest image: a thread loads S keys of each
+// kind whatever its image, clamped reads beyond it.
+//
+// Bound by the latency of its phases (a dozen barriers of sixteen wavefronts, a
+// round trip to memory) and by VALU issue in the two passes over all tokens.
+// A workgroup of the 4 x 18432 clips, us from its start, against the kernel that
+// bucketed every key from LDS and all of X^rem in every workgroup: samples ranked
+// 2.7, keys and first histogram 6.5 (6.6), boundary 8.6 (12), second pass 12-13
+// (16), own tokens' histogram and scan 14 (20), ranked 15 (23).  Calls: 4 x
+// 18432 tokens 320 -> 301 us, 32 images of up to 16384 969 -> 944, 16 x 2880 193
+// -> 189, selection alone of 24 images of up to 18000 tokens 39 -> 28 (at lambda =
+// 1, one workgroup an image, images of 4089 to 8162 tokens: 2 us slower).  Tried
+// and left out: the keys in registers instead of LDS (19 + 19 a thread, every
+// pass unrolled over them: 10000 instructions, not run); comparisons of (key,
+// index) pairs in every pass (second pass 1.2 us more); variants of the second
+// pass without Stage II for K2 = 0 (one more copy of its code: every pass 1 us
+// slower, K2 = 0 no faster); value buckets over sampled quantiles with the tails
+// clamped into the end buckets (a tail of 3 % of 18000 tokens went to the radix
+// sort: 56 us).
+template <int S>
+__global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int G = a.groups > 0 ? a.groups : 1;
+    const int local = (int)blockIdx.x / G, part = (int)blockIdx.x % G;
+    const int img = a.img0 + local;
+    const Img d = image_of(a, local);
+    const int N = d.n, K1 = d.k1, K2 = d.k2, R = N - K1;
+    const bool split = G > 1 && K2 > 0 && R >= kShareRem;   // as select_shares
+    if (part > 0 && !split) return;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    const LdsLayout L = lds_layout(N);
+    uint32_t* ks = reinterpret_cast<uint32_t*>(smem + L.ks);
+    uint32_t* ki = reinterpret_cast<uint32_t*>(smem + L.ki);
+    uint32_t* bimp = reinterpret_cast<uint32_t*>(smem + L.bimp);
+    uint32_t* bsel = reinterpret_cast<uint32_t*>(smem + L.bsel);
+    uint32_t* H = reinterpret_cast<uint32_t*>(smem + L.area);
+    uint32_t* cur = H + kBuckets;
+    uint32_t* slots = reinterpret_cast<uint32_t*>(smem + L.slots);
+    uint32_t* misc = reinterpret_cast<uint32_t*>(smem + L.misc);
+    uint64_t* own64 = reinterpret_cast<uint64_t*>(misc + kMOwn);
+    const float* fi = a.key_imp + d.row_off;
+    const float* fs = a.key_s + d.row_off;
+
+    // ---- keys, samples, ranges -------------------------------------------------
+    const float* fq = w == 0 ? fi : fs;   // 64 samples of either kind, ranked by wavefronts 0 and 1
+    const int iq = sample_index(N, lane) + (N > kWave ? (int)scatter(lane, (uint32_t)N / kWave) : 0);
+    const float vq = fq[min(iq, N - 1)];
+    int ia = 0, ib = 0;   // one block of the shared image's samples, and one it is compared with
+    if (split) {
+        ia = sample_token((w & 1) * kWave + lane, N);
+        ib = sample_token((w >> 1 & 1) * kWave + lane, N);
+    }
+    const float va = fs[ia], vb = fs[ib];
+    __builtin_amdgcn_sched_barrier(0);   // the samples' loads leave first
+    float vi[S], vs[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        const uint32_t at = 4u * (uint32_t)min(u * kThreads + tid, N - 1);   // 32 bits: base + offset loads
+        vi[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(fi) + at);
+        vs[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(fs) + at);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    H[tid] = 0u;
+    if (tid == 0) misc[kMCount] = 0u;
+    // Stage I's first range: the samples about three standard deviations to
+    // either side of rank 64 K1 / N; past the ends, three times as far as it is
+    // wide (one image in ten missed T with 2.5 and once: 2 to 4 us each)
+    const float at = (float)kWave * (float)K1 / (float)N;
+    const float off = 3.0f * sqrtf(at * fmaxf((float)kWave - at, 0.f) / (float)kWave) + 3.0f;
+    const int last = min(N, kWave) - 1;
+    const int rlo = (int)floorf(at - off), rhi = (int)ceilf(at + off);
+    const uint32_t qkey = iq < N ? order_key(vq) : 0xffffffffu;
+    uint64_t* rows = reinterpret_cast<uint64_t*>(cur + kSRows);
+    uint16_t* ranks = reinterpret_cast<uint16_t*>(cur + kSRanks);
+    uint32_t* sorted_keys = cur + kSSorted;
+    if (w == 0)
+        sample_quantiles<8>(qkey, lane, rows, N > kWave ? max(rlo, 0) : 0, N > kWave ? min(rhi, last) : last,
+                            &misc[kMBracket]);
+    if (w == 1 && !split)
+        sample_quantiles<8>(qkey, lane, rows + kWave, N > kWave ? 1 : 0, N > kWave ? kWave - 2 : last, &misc[kMQuant]);
+    const uint64_t smine = pair_of(order_key(va), (uint32_t)ia);
+    if (split) {   // a quarter of the other block's samples each
+        const uint64_t other = pair_of(order_key(vb), (uint32_t)ib);
+        uint32_t r = 0;
+#pragma unroll
+        for (int j = 0; j < kWave / 4; ++j) r += lane_u64(other, (w >> 2) * (kWave / 4) + j) < smine ? 1u : 0u;
+        ranks[(w >> 1) * kSample + (w & 1) * kWave + lane] = (uint16_t)r;
+    }
+    lds_barrier();   // the keys stay in flight
+    const uint32_t r0 = (uint32_t)(part * kSample / G), r1 = (uint32_t)((part + 1) * kSample / G);
+    if (split && tid < kSample) {   // `smine` is sample tid here
+        uint32_t r = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) r += ranks[j * kSample + tid];
+        sorted_keys[r] = (uint32_t)(smine >> 32);
+        if (r == r0) own64[0] = smine;
+        if (r == r1) own64[1] = smine;
+    }
+    const bool staged = K1 > 0 && K1 < N;   // Stage I has a choice to make
+    uint32_t lo = misc[kMBracket], hi = misc[kMBracket + 1];
+    if (N > kWave) {
+        const uint32_t wide = min(hi - lo, 0x40000000u) * 3u;
+        if (rlo < 0) lo = lo > wide ? lo - wide : 0u;
+        if (rhi > last) hi = hi < 0xffffffffu - wide ? hi + wide : 0xffffffffu;
+    }
+    const int sh = range_shift(lo, hi);
+
+    // ---- keys to LDS, the first range's histogram -----------------------------------
+    uint32_t nlo_s = 0, hi_s = 0, wave_below = 0;
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        const int i = u * kThreads + tid;
+        if (i < N) {
+            const uint32_t qi = order_key(vi[u]), qs = order_key(vs[u]);
+            ki[i] = qi;
+            ks[i] = qs;
+            nlo_s = max(nlo_s, ~qs);
+            hi_s = max(hi_s, qs);
+            if (staged) {
+                wave_below += (uint32_t)__popcll(__ballot(qi < lo));   // lane 0 is in every tile's ballot
+                if (qi - lo <= hi - lo) atomicAdd(&H[(qi - lo) >> sh], 1u);
+            }
+        }
+    }
+    nlo_s = wave_max_u32(nlo_s);
+    hi_s = wave_max_u32(hi_s);
+    if (lane == 0) {
+        slots[w] = nlo_s;
+        slots[kW + w] = hi_s;
+    }
+    Boundary bd{};
+    if (staged) {
+        uint32_t below, inside;
+        stage1_scan(wave_below, (uint32_t)K1, H, misc, slots + 4 * kW, slots + 5 * kW, below, inside);
+        bd = stage1_boundary(ki, N, (uint32_t)K1, lo, hi, below, inside, H, misc, slots + 4 * kW, slots + 5 * kW);
+    } else {
+        __syncthreads();
+    }
+    const uint32_t ksmin = ~max_all(slots, lane), ksmax = max_all(slots + kW, lane);
+
+    // ---- X^imp and the own tokens of X^rem ------------------------------------------
+    // A share's end is a key, or a pair where the sampled key repeats (its
+    // neighbours decide: the workgroups on both sides of it read the same).
+    Share own_range{0ull, 0ull, !(split && part < G - 1)};
+    bool exact = !staged || bd.tie;
+    auto share_end = [&](uint32_t r, uint64_t pair) {
+        const uint32_t k = sorted_keys[r];
+        const bool repeats = k == sorted_keys[r - 1] || k == sorted_keys[r + 1] || k == 0u;
+        exact |= repeats;
+        return repeats ? pair : pair_of(k, 0u);
+    };
+    if (split && part > 0) own_range.lo = share_end(r0, own64[0]);
+    if (!own_range.open) own_range.hi = share_end(r1, own64[1]);
+    uint32_t qlo = split ? sorted_keys[r0] : misc[kMQuant];   // value range of the buckets
+    uint32_t qhi = split ? sorted_keys[min(r1, (uint32_t)kSample - 1u)] : misc[kMQuant + 1];
+    {   // at the ends of X^rem, out to its own range unless outliers stretch that
+        // (a share of few samples is narrow, and half of an outermost one lies beyond them)
+        const float w0 = key_value(qhi) - key_value(qlo), far = (split ? (float)G : 1.5f) * w0;
+        if (part == 0 && key_value(qlo) - key_value(ksmin) <= far) qlo = ksmin;
+        if (own_range.open && key_value(ksmax) - key_value(qhi) <= far) qhi = ksmax;
+    }
+    const Bucketing bk = make_bucketing(qlo, qhi, ksmin, ksmax, kBuckets);
+    uint64_t* members = reinterpret_cast<uint64_t*>(cur);
+    const uint64_t imp_end = staged ? pair_of(bd.lo, bd.ilo) : K1 > 0 ? ~0ull : 0ull;
+    uint32_t* imp_bits = !split || part == 0 ? bimp : nullptr;
+    uint32_t own = 0, rem_below = 0;   // own: bit u, slot u
+    auto pass = [&](auto ex) {
+        second_pass<decltype(ex)::value>(ki, ks, N, bd, imp_end, staged, own_range, members, &misc[kMCount],
+                                         imp_bits, split ? nullptr : bsel, own, rem_below);
+    };
+    if (__builtin_amdgcn_readfirstlane(exact)) pass(std::true_type{});   // the same in every thread
+    else pass(std::false_type{});
+    __syncthreads();
+    int extra = -1;   // a boundary member that is an own token
+    if (staged) {
+        const uint32_t m = min(misc[kMCount], kMembers);
+        if (tid < (int)m) {
+            const uint64_t me = members[tid];
+            const uint32_t i = (uint32_t)me;
+            uint32_t r = 0;
+            for (uint32_t j = 0; j < m; ++j) r += members[j] < me ? 1u : 0u;
+            bool below = false;
+            if (r < bd.need) {
+                if (imp_bits) atomicOr(&bimp[i >> 5], 1u << (i & 31));
+                if (!split) atomicOr(&bsel[i >> 5], 1u << (i & 31));
+            } else {
+                const uint64_t ps = pair_of(ks[i], i);
+                below = ps < own_range.lo;
+                if (!below && (own_range.open || ps < own_range.hi)) extra = (int)i;
+            }
+            rem_below += (uint32_t)__popcll(__ballot(below));   // lane 0 takes part if any lane does
+        }
+    }
+    const size_t wbase = (size_t)(d.row_off >> 5) + 2 * (size_t)img;
+    if (K2 > 0) {
+        const Stride sp{(uint32_t)d.t, (uint32_t)R, (uint32_t)K2, a.stride_real != 0};
+        uint32_t* pick = split ? a.gsel + wbase : bsel;
+        auto keep = [&](uint32_t i) { atomicOr(&pick[i >> 5], 1u << (i & 31)); };
+        auto for_own = [&](auto f) {   // every own token of this thread
+            for (uint32_t o = own; o; o &= o - 1u) f((__ffs((int)o) - 1) * kThreads + tid);
+            if (extra >= 0) f(extra);
+        };
+        for_own([&](int i) { atomicAdd(&H[bucket_of(bk, ks[i], kBuckets)], 1u); });
+        __syncthreads();
+        if (split && part == 0)
+            for (int i = tid; i < (N + 31) / 32; i += kThreads) a.gimp[wbase + i] = bimp[i];
+        const uint32_t c = H[tid];
+        const uint32_t inc = wave_scan_add(c), sq = wave_sum_u32(c * c);   // at most N^2
+        if (lane == kWave - 1) slots[w] = inc;
+        if (lane == 0) {
+            slots[kW + w] = sq;
+            slots[2 * kW + w] = rem_below;
+        }
+        __syncthreads();
+        cur[tid] = inc - c + sum_before(slots, w, lane);
+        const int m = (int)sum_before(slots, kW, lane);
+        const uint32_t base = sum_before(slots + 2 * kW, kW, lane);
+        const bool sorted = sum_before(slots + kW, kW, lane) > kCountFixed + kCountPer * (uint32_t)m;
+        __syncthreads();
+        // Both list forms: add the own tokens at their buckets' cursors, then a
+        // thread per listed token counts the smaller members of its bucket.
+        auto list_own = [&](auto put) {
+            for_own([&](int i) { put(atomicAdd(&cur[bucket_of(bk, ks[i], kBuckets)], 1u), ks[i], i); });
+            __syncthreads();
+        };
+        if (sorted) {
+            // the tokens left out (G = 1: X^imp, as it is)
+            const int words = 2 * ((N + kWave - 1) / kWave);
+            if (split) {
+                for (int i = tid; i < words; i += kThreads) bimp[i] = 0xffffffffu;
+                __syncthreads();
+                for_own([&](int i) { atomicAnd(&bimp[i >> 5], ~(1u << (i & 31))); });
+            }
+            __syncthreads();
+            uint16_t* idx = reinterpret_cast<uint16_t*>(ki);
+            const uint32_t top = ksmin ^ ksmax;   // bits above its highest are the same in every key
+            const uint16_t* order = radix_sort(ks, bimp, N, m, top ? 0xffffffffu >> __clz((int)top) : 0u, idx, idx + N,
+                                               reinterpret_cast<uint16_t*>(H), slots + 4 * kW, slots + 5 * kW);
+            for (int j = tid; j < m; j += kThreads)
+                if (sp.picks(base + (uint32_t)j)) keep(order[j]);
+        } else if (8 * (size_t)m <= L.list_bytes) {
+            uint64_t* list = reinterpret_cast<uint64_t*>(smem + L.list);
+            list_own([&](uint32_t at, uint32_t key, int i) { list[at] = pair_of(key, (uint32_t)i); });
+            for (int j = tid; j < m; j += kThreads) {
+                const uint64_t me = list[j];
+                const int b = bucket_of(bk, (uint32_t)(me >> 32), kBuckets);
+                const uint32_t n = H[b];
+                if (sp.picks(base + rank_in(list, cur[b] - n, n, me))) keep((uint32_t)me);
+            }
+        } else {
+            uint16_t* list = reinterpret_cast<uint16_t*>(ki);
+            list_own([&](uint32_t at, uint32_t, int i) { list[at] = (uint16_t)i; });
+            for (int j = tid; j < m; j += kThreads) {
+                const uint32_t i = list[j], key = ks[i];
+                const int b = bucket_of(bk, key, kBuckets);
+                const uint32_t end = cur[b], beg = end - H[b];
+                uint32_t r = beg;
+#pragma unroll 4
+                for (uint32_t p = beg; p < end; ++p) r += pair_of(ks[list[p]], list[p]) < pair_of(key, i) ? 1u : 0u;
+                if (sp.picks(base + r)) keep(i);
+            }
+        }
+    }
+    if (split) return;   // emit_kernel writes the output of a shared image
+    __syncthreads();
+    const int tw = tile_word(N);
+    emit(a, d, tw >= 0 ? *reinterpret_cast<const uint64_t*>(bsel + tw) : 0ull,
+         tw >= 0 ? *reinterpret_cast<const uint64_t*>(bimp + tw) : 0ull, slots + 6 * kW);
+}
+
+// Output of the images select_kernel shared between workgroups: X^imp and the
+// picks from the global bitmaps (which are cleared for the next call), then
+// the ordered output (each lane reads its own tile's words).  One workgroup per image of the launch.
+__global__ __launch_bounds__(kThreads) void emit_kernel(SelectArgs a)
+{
+    __shared__ uint32_t row[kW];
+    const int G = a.groups > 0 ? a.groups : 1;
+    const int local = (int)blockIdx.x;
+    const int img = a.img0 + local;
+    const Img d = image_of(a, local);
+    const int N = d.n, K1 = d.k1, K2 = d.k2;
+    if (!(G > 1 && K2 > 0 && N - K1 >= kShareRem)) return;   // emitted by select_kernel
+    const size_t wbase = (size_t)(d.row_off >> 5) + 2 * (size_t)img;
+    const int words = (N + 31) / 32, tw = tile_word(N);
+    uint64_t sel = 0, imp = 0;
+    if (tw >= 0) {
+        const uint32_t* gi = a.gimp + wbase + tw;
+        uint32_t* gs = a.gsel + wbase + tw;
+        const bool two = tw + 1 < words;
+        const uint32_t i0 = gi[0], s0 = gs[0], i1 = two ? gi[1] : 0u, s1 = two ? gs[1] : 0u;
+        gs[0] = 0u;
+        if (two) gs[1] = 0u;
+        imp = (uint64_t)i1 << 32 | i0;
+        sel = imp | ((uint64_t)s1 << 32 | s0);
+    }
+    emit(a, d, sel, imp, row);
+}
+
+// ---- images of at most kSmallSelectN tokens: one token per thread ------------
+//
+// Both stages are ranked in the same passes.  Every token gets its exact rank
+// in (Stage II key, index) order among all N tokens, and its place relative
+// to K1 in (Stage I key, index) order (counted exactly only inside the bucket
+// that holds the K1 boundary); X^imp is the places below K1, and a token of X^rem ranks in X^rem as
+// its Stage II rank minus the X^imp tokens ranked below it (read from a
+// bitmap of X^imp in Stage II rank order), which decides the stride picks.
+// Ranks come from value buckets and exact counting inside a bucket: bucket =
+// clamp(floor((v - lo) nb / (hi - lo)), 0, nb - 1) is non-decreasing in the
+// key, so rank = (tokens in lower buckets) + (members of the token's bucket
+// smaller in (key, index) order).  lo and hi are about the 1.5 % and 98.5 %
+// quantiles of a 64-key sample, so outliers (all-zero rows, zero-norm states)
+// land in the two end buckets instead of crowding the bulk into a few; when
+// the sample's range is not a finite positive float width, buckets are equal
+// ranges of the order-preserving key itself.  All keys equal: rank = index.
+// Phases are separated by eight workgroup barriers.  With a fused gather, G
+// workgroups share an image: each repeats the selection and copies every G-th
+// share of the kept rows (group 0 writes out_idx / out_src / out_rows).
+
+struct SmallLayout {
+    size_t hi, hs, si, ss, li, ls, samp, slots, misc, imps, kept, total;
+};
+
+__host__ __device__ inline SmallLayout small_layout(int T)
+{
+    SmallLayout L;
+    size_t o = 0;
+    L.hi = o;  o += 4 * (size_t)T;            // Stage I histogram, then cursors
+    L.hs = o;  o += 4 * (size_t)T;            // Stage II histogram, then cursors
+    L.si = o;  o += 4 * ((size_t)T + 1);      // Stage I bucket starts
+    L.ss = o;  o += 4 * ((size_t)T + 1);      // Stage II bucket starts
+    o = align_up(o, 16);
+    L.li = o;  o += 8 * (size_t)T;            // (key << 32 | index) in Stage I bucket order
+    L.ls = o;  o += 8 * (size_t)T;            // the same for Stage II
+    L.samp = o; o += 8 * 128;                 // 64-key samples of both keys, (key << 6 | k)
+    L.slots = o; o += 4 * 8 * kW;             // per-wavefront partial values
+    L.misc = o; o += 4 * 16;                  // broadcast slots
+    L.imps = o; o += 4 * 32;                  // X^imp bitmap in Stage II rank order
+    L.kept = o; o += 4 * (size_t)T;           // token of each output slot (fused gather)
+    L.total = o;
+    return L;
 }
 
 typedef uint32_t u32x4s __attribute__((ext_vector_type(4)));
@@ -1262,14 +1080,17 @@ __global__ __launch_bounds__(kSmallSelectN) void select_small_kernel(SelectArgs 
     uint32_t* kept = reinterpret_cast<uint32_t*>(smem + L.kept);
 
     // ---- keys, samples, per-wavefront ranges ----------------------------------
-    uint32_t ki = 0, ks = 0;
-    if (valid) {
-        ki = order_key(a.key_imp[d.row_off + tid]);
-        ks = order_key(a.key_s[d.row_off + tid]);
-    }
+    // every load in one burst: a token's keys, and a sample of each kind
+    const float* fi = a.key_imp + d.row_off;
+    const float* fs = a.key_s + d.row_off;
+    const int it = min(tid, N - 1), iq = sample_index(N, lane), iqc = min(iq, N - 1);
+    const float vi = fi[it], vs = fs[it], ui = fi[iqc], us = fs[iqc];
+    const uint32_t ki = valid ? order_key(vi) : 0u, ks = valid ? order_key(vs) : 0u;
     // the quantiles of both keys, by wavefronts 0 and 1 (0 alone for N <= 64)
-    if (w == 0) sample_quantiles(a.key_imp + d.row_off, N, lane, samp, &misc[0]);
-    if (w == (nw > 1 ? 1 : 0)) sample_quantiles(a.key_s + d.row_off, N, lane, samp + kWave, &misc[2]);
+    const int q_lo = N > kWave ? 1 : 0, q_hi = N > kWave ? kWave - 2 : N - 1;
+    if (w == 0) sample_quantiles(iq < N ? order_key(ui) : 0xffffffffu, lane, samp, q_lo, q_hi, &misc[0]);
+    if (w == (nw > 1 ? 1 : 0))
+        sample_quantiles(iq < N ? order_key(us) : 0xffffffffu, lane, samp + kWave, q_lo, q_hi, &misc[2]);
     Hi[tid] = 0u;
     Hs[tid] = 0u;
     kept[tid] = 0xffffffffu;
@@ -1442,7 +1263,7 @@ int select_threads(int nmax)
 
 bool select_shares(const ImageDesc& d)
 {
-    return d.k2 > 0 && d.n - d.k1 >= kDenseRem;
+    return d.k2 > 0 && d.n - d.k1 >= kShareRem;
 }
 
 int select_groups(int64_t n_large, int cus)
@@ -1461,18 +1282,17 @@ size_t select_gsel_words(int64_t max_tokens, int max_images)
 size_t select_lds_bytes(int n, int threads)
 {
     (void)threads;
-    return launch_lds(n);
+    return n <= kMaxSlots * kThreads ? launch_lds(n) : SIZE_MAX;
 }
 
 hipError_t select_prepare(int lds_limit)
 {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_small_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&emit_kernel),
+    for (auto kernel : {select_kernel<4>, select_kernel<10>, select_kernel<kMaxSlots>}) {
+        const void* k = reinterpret_cast<const void*>(kernel);
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
+        if (e != hipSuccess) return e;
+    }
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&select_small_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
 }
 
@@ -1499,10 +1319,11 @@ hipError_t launch_select(const SelectArgs& a, int nmax, hipStream_t s)
     }
     const size_t lds = launch_lds(nmax);
     const int groups = a.groups > 0 ? a.groups : 1;
-    hipLaunchKernelGGL(select_kernel, dim3(a.nimg * groups), dim3(kThreads), lds, s, a);
+    auto kernel = nmax <= 4 * kThreads ? select_kernel<4>
+                  : nmax <= 10 * kThreads ? select_kernel<10> : select_kernel<kMaxSlots>;
+    hipLaunchKernelGGL(kernel, dim3(a.nimg * groups), dim3(kThreads), lds, s, a);
     if (groups > 1) {
-        const size_t elds = 8 * (2 * (((size_t)nmax + 63) / 64)) + 4 * 8 * kW;
-        hipLaunchKernelGGL(emit_kernel, dim3(a.nimg), dim3(kThreads), elds, s, a);
+        hipLaunchKernelGGL(emit_kernel, dim3(a.nimg), dim3(kThreads), 0, s, a);
     }
     return hipGetLastError();
 }
