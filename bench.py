@@ -76,7 +76,7 @@ def score_source_sha() -> str:
     """sha256 of the scoring kernel's sources: the kernel, its interface header
     and the wavefront helpers it uses."""
     h = hashlib.sha256()
-    for f in ("tr_score.hip", "tr_score.h", "tr_wave.h"):
+    for f in ("tr_score.hip", "tr_score.h", "tr_row.h", "tr_wave.h"):
         with open(os.path.join(ROOT, "paper_2607_13500_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

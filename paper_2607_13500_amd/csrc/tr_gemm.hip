@@ -10,7 +10,9 @@
 //     hidden activations) and P = x' its input, these are Eq. (6)'s three sums,
 //     so the Stage II score needs no further pass over X_pre or X_post.  The
 //     sums use C as stored (rounded to bf16), so the score is Eq. (6) on the
-//     x'' the caller receives, as an unfused scoring pass would compute it.
+//     x'' the caller receives, as an unfused scoring pass would compute it; a
+//     row whose squared norms leave that pass's range is read again and scaled
+//     as there (cos_finish_kernel).
 //
 // Two kernels for gfx950 (64-wide wavefronts, 32x32x16 bf16 MFMA), both with
 // the same per-element MFMA sequence (k ascending in steps of 16), so they give
@@ -32,6 +34,7 @@
 #include <type_traits>
 
 #include "tr_internal.h"
+#include "tr_row.h"
 #include "tr_wave.h"
 
 namespace tr {
@@ -53,6 +56,11 @@ __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w 
 
 // bf16 round-to-nearest-even of an fp32 value (NaN stays NaN), in hardware.
 __device__ __forceinline__ uint16_t to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+
+// A partial sum of squares that came out as 0 although some of its elements are
+// not (their products underflow): a value below every accepted norm in its
+// place, so that only rows of zeros end with a norm of exactly 0.
+__device__ __forceinline__ float mark_underflow(float sum, bool some) { return sum == 0.f && some ? 0x1p-126f : sum; }
 
 template <bool GATHER, bool COS>
 __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a)
@@ -170,6 +178,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a)
             const int m = m0 + rl;
             const bool ok = m < a.M;
             float dot = 0.f, pp = 0.f, cc = 0.f;
+            [[maybe_unused]] bool some_p = false, some_c = false;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int n = n0 + wn * 64 + j * 32 + (lane & 31);
@@ -181,9 +190,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a)
                     dot = fmaf(p, c, dot);
                     pp = fmaf(p, p, pp);
                     cc = fmaf(c, c, cc);
+                    some_p |= p != 0.f;
+                    some_c |= c != 0.f;
                 }
             }
             if constexpr (COS) {
+                pp = mark_underflow(pp, some_p);
+                cc = mark_underflow(cc, some_c);
                 // sum over the 32 lanes of this half (same row): lane 31 / 63 ends with it
                 dot = half_sum(dot);
                 pp = half_sum(pp);
@@ -360,6 +373,9 @@ __device__ __forceinline__ void finish_block(const GemmArgs& a, const f32x16 (&a
                 pp = dot2(p[g][k], p[g][k], pp);
                 cc = dot2(v[k], v[k], cc);
             }
+            auto some = [](u32x4 x) { return ((x[0] | x[1] | x[2] | x[3]) & 0x7fff7fffu) != 0u; };   // not all +-0
+            pp = mark_underflow(pp, some(p[g]));
+            cc = mark_underflow(cc, some(v));
             d = sum8(d);
             pp = sum8(pp);
             cc = sum8(cc);
@@ -633,22 +649,40 @@ __global__ __launch_bounds__(kPThreads, 1) void gemm_large_kernel(GemmArgs a)
     }
 }
 
-// s = dot / (|P| |C|) from the per-tile partials, summed in tile order; the
-// same zero-norm reading as the scoring kernel (s = 0).
-__global__ __launch_bounds__(256) void cos_finish_kernel(const float* part, int stride, int cols, int M, float* s)
+// s = dot / (|P| |C|) from the per-tile partials, summed in tile order, with the
+// scoring kernel's reading of its sums: a zero vector gives s = 0, and a row
+// whose squared norms leave the accepted range (states of magnitude 2^-75 to
+// 2^-30, whose products underflow in part, or beyond 2^63) is read again by the
+// wavefront, each vector scaled by its own maximum.  A wavefront takes few rows
+// because it reads them again one by one.
+constexpr int kFinishRows = 16;   // rows of a wavefront
+
+__global__ __launch_bounds__(256) void cos_finish_kernel(GemmArgs a, int cols)
 {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= M) return;
-    const float* p = part + (int64_t)m * stride * 3;
-    float dot = 0.f, n1 = 0.f, n2 = 0.f;
-    for (int c = 0; c < cols; ++c) {
-        dot += p[3 * c];
-        n1 += p[3 * c + 1];
-        n2 += p[3 * c + 2];
-    }
+    const int lane = threadIdx.x & 63;
+    const int r0 = ((int)blockIdx.x * (256 / kWave) + (int)(threadIdx.x / kWave)) * kFinishRows;
+    const int m = r0 + lane;
     float v = 0.f;
-    if (n1 > 0.f && n2 > 0.f) v = dot / (sqrtf(n1) * sqrtf(n2));
-    s[m] = v;
+    bool again = false;
+    if (lane < kFinishRows && m < a.M) {
+        const float* p = a.part + (int64_t)m * a.part_cols * 3;
+        float dot = 0.f, n1 = 0.f, n2 = 0.f;
+        for (int c = 0; c < cols; ++c) {
+            dot += p[3 * c];
+            n1 += p[3 * c + 1];
+            n2 += p[3 * c + 2];
+        }
+        if (cos_in_range(n1, n2)) v = dot / (sqrtf(n1) * sqrtf(n2));
+        else again = n1 != 0.f && n2 != 0.f;
+    }
+    for (uint64_t left = __ballot(again); left; left &= left - 1) {
+        const int l = __ffsll((long long)left) - 1;
+        const float s = cos_reread<true>(reinterpret_cast<const char*>(a.P) + (int64_t)(r0 + l) * a.ldp * 2,
+                                         reinterpret_cast<const char*>(a.C) + (int64_t)(r0 + l) * a.ldc * 2, a.N,
+                                         lane).s;
+        if (lane == l) v = s;
+    }
+    if (lane < kFinishRows && m < a.M) a.s_out[m] = v;
 }
 
 // The large kernel takes every shape whose buffer offsets (rows of a tile, or
@@ -770,8 +804,9 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !cos) return e;
-    hipLaunchKernelGGL(cos_finish_kernel, dim3((a.M + 255) / 256), dim3(256), 0, s, a.part, a.part_cols, (a.N + bn - 1) / bn,
-                       a.M, a.s_out);
+    constexpr int kRows = kFinishRows * (256 / kWave);
+    hipLaunchKernelGGL(cos_finish_kernel, dim3((unsigned)(((int64_t)a.M + kRows - 1) / kRows)), dim3(256), 0, s, a,
+                       (a.N + bn - 1) / bn);
     return hipGetLastError();
 }
 

@@ -173,6 +173,42 @@ def run_mlp_out_cos_parity(M, Dc, Hd):
     r.close()
 
 
+@pytest.mark.parametrize("ldh", [None, 1 << 22])
+def test_mlp_out_cos_at_any_magnitude(ldh):
+    """s of states whose squares underflow or overflow fp32, against the oracle
+    on the stored x'' and against the scoring kernel: x' and x'' scaled by powers
+    of two, alone and together, rows of zeros, and one large element among tiny
+    ones.  A row stride of 2^22 elements takes the kernel with 64-bit offsets."""
+    M, Dc, Hd = 90, 384, 128
+    say("mlp_out_cos magnitudes", M, Dc, Hd, "ldh", ldh)
+    Xpre, H, W2 = mlp_inputs(M, Dc, Hd, 31)
+    e = [-110, -75, -70, -66, -63, -40, -30, -29, 0, 40, 62, 64, 66, 100]
+    pairs = [(a, 0) for a in e] + [(0, a) for a in e] + [(a, a) for a in e] + [(-70, 66), (66, -70), (-110, 100)]
+    for m, (a, b) in enumerate(pairs):
+        Xpre[m] = (Xpre[m].double() * 2.0 ** a).to(torch.bfloat16)
+        H[m] = (H[m].double() * 2.0 ** b).to(torch.bfloat16)
+    Xpre[len(pairs), 7], Xpre[len(pairs) + 1, 5:] = 2.0 ** 70, 0.0
+    Xpre[len(pairs) + 1, :5] = 2.0 ** -80
+    Xpre[len(pairs) + 2], H[len(pairs) + 3] = 0.0, 0.0
+    r = reducer(D=Dc, Dc=Dc, max_tokens=M)
+    Hd_dev = H.to(DEV)
+    if ldh is not None:
+        wide = torch.empty((M - 1) * ldh + Hd, dtype=torch.bfloat16, device=DEV).as_strided((M, Hd), (ldh, 1))
+        wide.copy_(Hd_dev)
+        Hd_dev = wide
+    Xpost, s = r.mlp_out_cos(Hd_dev, W2.to(DEV), Xpre.to(DEV))
+    _, s_unfused, _ = r.score(None, Xpre.to(DEV), Xpost)
+    torch.cuda.synchronize()
+    xp, xq = oracle.as_f64(Xpre), oracle.as_f64(Xpost.cpu())
+    ref = np.array([oracle.cosine(xp[m], xq[m]) for m in range(M)])
+    got = s.double().cpu().numpy()
+    err = np.abs(got - ref)
+    assert np.all(err <= parity.TOL * np.maximum(parity.S_FLOOR, np.abs(ref))), (np.argmax(err), err.max())
+    assert got[len(pairs) + 2] == 0.0 and got[len(pairs) + 3] == 0.0
+    assert (s - s_unfused).abs().max().item() <= 2e-6
+    r.close()
+
+
 def test_fused_mlp_module_parity():
     """Stage II key from the fused epilogue, Stage I from X: the module's
     selection against the oracle's (H2 of X, cos(x', x'') on the stored x''),
