@@ -261,7 +261,7 @@ __device__ __forceinline__ u32x4 buffer_of(const void* p, int64_t bytes)
 __device__ __forceinline__ void load_lds(u32x4 r, uint32_t lds, uint32_t voff, uint32_t soff)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory");
+                 :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory", "m0");
 }
 
 // At most n of this wavefront's loads still in flight.
