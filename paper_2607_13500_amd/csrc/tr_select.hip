@@ -1080,16 +1080,21 @@ __global__ __launch_bounds__(kSmallSelectN) void select_small_kernel(SelectArgs 
     uint32_t* kept = reinterpret_cast<uint32_t*>(smem + L.kept);
 
     // ---- keys, samples, per-wavefront ranges ----------------------------------
-    // every load in one burst: a token's keys, and a sample of each kind
+    // every load in one burst: a token's keys, and in the wavefront that ranks it
+    // a sample (every wavefront loading both: 30 images of 512 tokens 9.4 -> 9.9 us)
     const float* fi = a.key_imp + d.row_off;
     const float* fs = a.key_s + d.row_off;
     const int it = min(tid, N - 1), iq = sample_index(N, lane), iqc = min(iq, N - 1);
-    const float vi = fi[it], vs = fs[it], ui = fi[iqc], us = fs[iqc];
+    const float vi = fi[it], vs = fs[it];
+    float ui = 0.f, us = 0.f;
+    const int wu = __builtin_amdgcn_readfirstlane(w), ws = nw > 1 ? 1 : 0;
+    if (wu == 0) ui = fi[iqc];
+    if (wu == ws) us = fs[iqc];
     const uint32_t ki = valid ? order_key(vi) : 0u, ks = valid ? order_key(vs) : 0u;
     // the quantiles of both keys, by wavefronts 0 and 1 (0 alone for N <= 64)
     const int q_lo = N > kWave ? 1 : 0, q_hi = N > kWave ? kWave - 2 : N - 1;
-    if (w == 0) sample_quantiles(iq < N ? order_key(ui) : 0xffffffffu, lane, samp, q_lo, q_hi, &misc[0]);
-    if (w == (nw > 1 ? 1 : 0))
+    if (wu == 0) sample_quantiles(iq < N ? order_key(ui) : 0xffffffffu, lane, samp, q_lo, q_hi, &misc[0]);
+    if (wu == ws)
         sample_quantiles(iq < N ? order_key(us) : 0xffffffffu, lane, samp + kWave, q_lo, q_hi, &misc[2]);
     Hi[tid] = 0u;
     Hs[tid] = 0u;
