@@ -76,6 +76,7 @@ struct LdsLayout {
 
 __host__ __device__ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) & ~(a - 1); }
 
+// Without Stage II (no image of the launch has K2 > 0) there is no ks and no list.
 //   ks    u32[n]        Stage II keys by token index
 //   ki    u32[n]        Stage I keys; once X^imp is known the list of the own
 //                       tokens (below), or the two u16[n] index buffers of the
@@ -93,13 +94,13 @@ __host__ __device__ inline size_t align_up(size_t v, size_t a) { return (v + a -
 //                       if they fit, else u16 indices.  n < kListN: a
 //                       region of u64[n], else the bytes of ki (a share of a
 //                       large image is far smaller)
-__host__ __device__ inline LdsLayout lds_layout(int n)
+__host__ __device__ inline LdsLayout lds_layout(int n, bool two = true)
 {
     LdsLayout L;
     const size_t nw = 2 * (((size_t)n + 63) / 64);
     size_t o = 0;
     L.ks = o;
-    o += 4 * (size_t)n;
+    if (two) o += 4 * (size_t)n;
     L.ki = o;
     o += 4 * (size_t)n;
     L.bimp = o;
@@ -115,7 +116,7 @@ __host__ __device__ inline LdsLayout lds_layout(int n)
     o += 4 * 16;
     if (n < kListN) {
         L.list = o;
-        L.list_bytes = 8 * (size_t)n;
+        L.list_bytes = two ? 8 * (size_t)n : 0;
         o += L.list_bytes;
     } else {
         L.list = align_up(L.ki, 8);
@@ -127,10 +128,10 @@ __host__ __device__ inline LdsLayout lds_layout(int n)
 
 // LDS a launch needs for images of at most nmax tokens: the largest layout of
 // any n <= nmax (it is not monotonic at kListN).
-__host__ __device__ inline size_t launch_lds(int nmax)
+__host__ __device__ inline size_t launch_lds(int nmax, bool two = true)
 {
-    const size_t big = lds_layout(nmax).total;
-    if (nmax < kListN) return big;
+    const size_t big = lds_layout(nmax, two).total;
+    if (nmax < kListN || !two) return big;
     const size_t small = lds_layout(kListN - 1).total;
     return big > small ? big : small;
 }
@@ -635,7 +636,7 @@ struct Share {
 // it the boundary and the share are ranges of keys.  The counts come from
 // ballots of single comparisons, combined as scalars: a ballot of a combined
 // condition costs two vector instructions more, and a tile has about ten.
-template <bool EXACT, bool FULL>   // FULL: every token read is one of the image
+template <bool EXACT, bool TWO, bool FULL>   // FULL: every token read is one of the image
 __device__ __forceinline__ void second_pass_step(const uint32_t* ki, const uint32_t* ks, int N, int u, const Boundary& bd,
                                                  uint64_t imp_end, bool members_left, const Share& sh,
                                                  uint64_t* members, uint32_t* count, uint32_t* bimp, uint32_t* bsel,
@@ -644,16 +645,16 @@ __device__ __forceinline__ void second_pass_step(const uint32_t* ki, const uint3
     const int lane = threadIdx.x & (kWave - 1), i0 = u * kThreads + (int)threadIdx.x;
     const uint64_t mhi = pair_of(bd.hi, bd.ihi);
     const uint32_t klo = (uint32_t)(sh.lo >> 32), khi = sh.open ? 0xffffffffu : (uint32_t)(sh.hi >> 32) - 1u;
-    uint32_t qi[kUnr], qs[kUnr];
+    uint32_t qi[kUnr], qs[kUnr] = {};
     if constexpr (FULL) {
 #pragma unroll
         for (int q = 0; q < kUnr; ++q) {
             qi[q] = ki[i0 + q * kThreads];
-            qs[q] = ks[i0 + q * kThreads];
+            if constexpr (TWO) qs[q] = ks[i0 + q * kThreads];
         }
     } else {
         read_keys(ki, i0, N, qi);
-        read_keys(ks, i0, N, qs);
+        if constexpr (TWO) read_keys(ks, i0, N, qs);
     }
 #pragma unroll
     for (int q = 0; q < kUnr; ++q) {
@@ -667,18 +668,18 @@ __device__ __forceinline__ void second_pass_step(const uint32_t* ki, const uint3
         const uint64_t vm = FULL ? ~0ull : __ballot(valid);
         const uint64_t mi = __ballot(imp) & vm;
         const uint64_t mm = EXACT && !members_left ? 0ull : __ballot(upto) & vm & ~mi;
-        rem_below += (uint32_t)__popcll(__ballot(below) & vm & ~(mi | mm));
+        if constexpr (TWO) rem_below += (uint32_t)__popcll(__ballot(below) & vm & ~(mi | mm));
         if (mm) append_member(mm, qi[q], i, members, count, lane);
         if (bimp && (FULL || tb < N)) {
             put_tile_bits(bimp, tb, mi, lane);
             if (bsel) put_tile_bits(bsel, tb, mi, lane);
         }
         const bool rem = valid && !(EXACT ? imp || (members_left && upto) : upto);   // imp implies upto
-        own |= rem && !below && under ? 1u << (u + q) : 0u;
+        if constexpr (TWO) own |= rem && !below && under ? 1u << (u + q) : 0u;
     }
 }
 
-template <bool EXACT>
+template <bool EXACT, bool TWO>
 __device__ __forceinline__ void second_pass(const uint32_t* ki, const uint32_t* ks, int N, const Boundary& bd,
                                             uint64_t imp_end, bool members_left, const Share& sh, uint64_t* members,
                                             uint32_t* count, uint32_t* bimp, uint32_t* bsel, uint32_t& own,
@@ -687,10 +688,10 @@ __device__ __forceinline__ void second_pass(const uint32_t* ki, const uint32_t* 
     int u = 0;
     if constexpr (!EXACT)
         for (; (u + kUnr) * kThreads <= N; u += kUnr)
-            second_pass_step<false, true>(ki, ks, N, u, bd, imp_end, members_left, sh, members, count, bimp,
+            second_pass_step<false, TWO, true>(ki, ks, N, u, bd, imp_end, members_left, sh, members, count, bimp,
                                                 bsel, own, rem_below);
     for (; u * kThreads < N; u += kUnr)
-        second_pass_step<EXACT, false>(ki, ks, N, u, bd, imp_end, members_left, sh, members, count, bimp, bsel,
+        second_pass_step<EXACT, TWO, false>(ki, ks, N, u, bd, imp_end, members_left, sh, members, count, bimp, bsel,
                                              own, rem_below);
 }
 
@@ -729,19 +730,22 @@ __device__ __forceinline__ int sample_token(int k, int N)
 // slower, K2 = 0 no faster); value buckets over sampled quantiles with the tails
 // clamped into the end buckets (a tail of 3 % of 18000 tokens went to the radix
 // sort: 56 us).
-template <int S>
+//
+// Without TWO no image of the launch has a Stage II (K1 = K, as at lambda = 1):
+// nothing of its keys is loaded, kept or ranked.
+template <int S, bool TWO>
 __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int G = a.groups > 0 ? a.groups : 1;
+    const int G = TWO && a.groups > 0 ? a.groups : 1;
     const int local = (int)blockIdx.x / G, part = (int)blockIdx.x % G;
     const int img = a.img0 + local;
     const Img d = image_of(a, local);
-    const int N = d.n, K1 = d.k1, K2 = d.k2, R = N - K1;
-    const bool split = G > 1 && K2 > 0 && R >= kShareRem;   // as select_shares
+    const int N = d.n, K1 = d.k1, K2 = TWO ? d.k2 : 0, R = N - K1;
+    const bool split = TWO && G > 1 && K2 > 0 && R >= kShareRem;   // as select_shares
     if (part > 0 && !split) return;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    const LdsLayout L = lds_layout(N);
+    const LdsLayout L = lds_layout(N, TWO);
     uint32_t* ks = reinterpret_cast<uint32_t*>(smem + L.ks);
     uint32_t* ki = reinterpret_cast<uint32_t*>(smem + L.ki);
     uint32_t* bimp = reinterpret_cast<uint32_t*>(smem + L.bimp);
@@ -755,7 +759,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
     const float* fs = a.key_s + d.row_off;
 
     // ---- keys, samples, ranges -------------------------------------------------
-    const float* fq = w == 0 ? fi : fs;   // 64 samples of either kind, ranked by wavefronts 0 and 1
+    const float* fq = !TWO || w == 0 ? fi : fs;   // 64 samples of either kind, ranked by wavefronts 0 and 1
     const int iq = sample_index(N, lane) + (N > kWave ? (int)scatter(lane, (uint32_t)N / kWave) : 0);
     const float vq = fq[min(iq, N - 1)];
     int ia = 0, ib = 0;   // one block of the shared image's samples, and one it is compared with
@@ -763,14 +767,14 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
         ia = sample_token((w & 1) * kWave + lane, N);
         ib = sample_token((w >> 1 & 1) * kWave + lane, N);
     }
-    const float va = fs[ia], vb = fs[ib];
+    const float va = TWO ? fs[ia] : 0.f, vb = TWO ? fs[ib] : 0.f;
     __builtin_amdgcn_sched_barrier(0);   // the samples' loads leave first
     float vi[S], vs[S];
 #pragma unroll
     for (int u = 0; u < S; ++u) {
         const uint32_t at = 4u * (uint32_t)min(u * kThreads + tid, N - 1);   // 32 bits: base + offset loads
         vi[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(fi) + at);
-        vs[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(fs) + at);
+        if constexpr (TWO) vs[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(fs) + at);
     }
     __builtin_amdgcn_sched_barrier(0);
     H[tid] = 0u;
@@ -789,7 +793,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
     if (w == 0)
         sample_quantiles<8>(qkey, lane, rows, N > kWave ? max(rlo, 0) : 0, N > kWave ? min(rhi, last) : last,
                             &misc[kMBracket]);
-    if (w == 1 && !split)
+    if (TWO && w == 1 && !split)
         sample_quantiles<8>(qkey, lane, rows + kWave, N > kWave ? 1 : 0, N > kWave ? kWave - 2 : last, &misc[kMQuant]);
     const uint64_t smine = pair_of(order_key(va), (uint32_t)ia);
     if (split) {   // a quarter of the other block's samples each
@@ -824,22 +828,27 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
     for (int u = 0; u < S; ++u) {
         const int i = u * kThreads + tid;
         if (i < N) {
-            const uint32_t qi = order_key(vi[u]), qs = order_key(vs[u]);
+            const uint32_t qi = order_key(vi[u]);
             ki[i] = qi;
-            ks[i] = qs;
-            nlo_s = max(nlo_s, ~qs);
-            hi_s = max(hi_s, qs);
+            if constexpr (TWO) {
+                const uint32_t qs = order_key(vs[u]);
+                ks[i] = qs;
+                nlo_s = max(nlo_s, ~qs);
+                hi_s = max(hi_s, qs);
+            }
             if (staged) {
                 wave_below += (uint32_t)__popcll(__ballot(qi < lo));   // lane 0 is in every tile's ballot
                 if (qi - lo <= hi - lo) atomicAdd(&H[(qi - lo) >> sh], 1u);
             }
         }
     }
-    nlo_s = wave_max_u32(nlo_s);
-    hi_s = wave_max_u32(hi_s);
-    if (lane == 0) {
-        slots[w] = nlo_s;
-        slots[kW + w] = hi_s;
+    if constexpr (TWO) {
+        nlo_s = wave_max_u32(nlo_s);
+        hi_s = wave_max_u32(hi_s);
+        if (lane == 0) {
+            slots[w] = nlo_s;
+            slots[kW + w] = hi_s;
+        }
     }
     Boundary bd{};
     if (staged) {
@@ -849,7 +858,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
     } else {
         __syncthreads();
     }
-    const uint32_t ksmin = ~max_all(slots, lane), ksmax = max_all(slots + kW, lane);
+    const uint32_t ksmin = TWO ? ~max_all(slots, lane) : 0u, ksmax = TWO ? max_all(slots + kW, lane) : 0u;
 
     // ---- X^imp and the own tokens of X^rem ------------------------------------------
     // A share's end is a key, or a pair where the sampled key repeats (its
@@ -864,9 +873,11 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
     };
     if (split && part > 0) own_range.lo = share_end(r0, own64[0]);
     if (!own_range.open) own_range.hi = share_end(r1, own64[1]);
-    uint32_t qlo = split ? sorted_keys[r0] : misc[kMQuant];   // value range of the buckets
-    uint32_t qhi = split ? sorted_keys[min(r1, (uint32_t)kSample - 1u)] : misc[kMQuant + 1];
-    {   // at the ends of X^rem, out to its own range unless outliers stretch that
+    uint32_t qlo = 0u, qhi = 0u;
+    if constexpr (TWO) {   // value range of the buckets
+        qlo = split ? sorted_keys[r0] : misc[kMQuant];
+        qhi = split ? sorted_keys[min(r1, (uint32_t)kSample - 1u)] : misc[kMQuant + 1];
+        // at the ends of X^rem, out to its own range unless outliers stretch that
         // (a share of few samples is narrow, and half of an outermost one lies beyond them)
         const float w0 = key_value(qhi) - key_value(qlo), far = (split ? (float)G : 1.5f) * w0;
         if (part == 0 && key_value(qlo) - key_value(ksmin) <= far) qlo = ksmin;
@@ -878,7 +889,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
     uint32_t* imp_bits = !split || part == 0 ? bimp : nullptr;
     uint32_t own = 0, rem_below = 0;   // own: bit u, slot u
     auto pass = [&](auto ex) {
-        second_pass<decltype(ex)::value>(ki, ks, N, bd, imp_end, staged, own_range, members, &misc[kMCount],
+        second_pass<decltype(ex)::value, TWO>(ki, ks, N, bd, imp_end, staged, own_range, members, &misc[kMCount],
                                          imp_bits, split ? nullptr : bsel, own, rem_below);
     };
     if (__builtin_amdgcn_readfirstlane(exact)) pass(std::true_type{});   // the same in every thread
@@ -896,16 +907,16 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
             if (r < bd.need) {
                 if (imp_bits) atomicOr(&bimp[i >> 5], 1u << (i & 31));
                 if (!split) atomicOr(&bsel[i >> 5], 1u << (i & 31));
-            } else {
+            } else if constexpr (TWO) {
                 const uint64_t ps = pair_of(ks[i], i);
                 below = ps < own_range.lo;
                 if (!below && (own_range.open || ps < own_range.hi)) extra = (int)i;
             }
-            rem_below += (uint32_t)__popcll(__ballot(below));   // lane 0 takes part if any lane does
+            if constexpr (TWO) rem_below += (uint32_t)__popcll(__ballot(below));   // lane 0 takes part if any lane does
         }
     }
     const size_t wbase = (size_t)(d.row_off >> 5) + 2 * (size_t)img;
-    if (K2 > 0) {
+    if (TWO && K2 > 0) {
         const Stride sp{(uint32_t)d.t, (uint32_t)R, (uint32_t)K2, a.stride_real != 0};
         uint32_t* pick = split ? a.gsel + wbase : bsel;
         auto keep = [&](uint32_t i) { atomicOr(&pick[i >> 5], 1u << (i & 31)); };
@@ -1292,7 +1303,8 @@ size_t select_lds_bytes(int n, int threads)
 
 hipError_t select_prepare(int lds_limit)
 {
-    for (auto kernel : {select_kernel<4>, select_kernel<10>, select_kernel<kMaxSlots>}) {
+    for (auto kernel : {select_kernel<4, true>, select_kernel<10, true>, select_kernel<kMaxSlots, true>,
+                        select_kernel<4, false>, select_kernel<10, false>, select_kernel<kMaxSlots, false>}) {
         const void* k = reinterpret_cast<const void*>(kernel);
         const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
         if (e != hipSuccess) return e;
@@ -1322,10 +1334,16 @@ hipError_t launch_select(const SelectArgs& a, int nmax, hipStream_t s)
         hipLaunchKernelGGL(select_small_kernel, dim3(a.nimg * G), dim3(T), small_layout(T).total, s, b);
         return hipGetLastError();
     }
-    const size_t lds = launch_lds(nmax);
-    const int groups = a.groups > 0 ? a.groups : 1;
-    auto kernel = nmax <= 4 * kThreads ? select_kernel<4>
-                  : nmax <= 10 * kThreads ? select_kernel<10> : select_kernel<kMaxSlots>;
+    bool two = false;
+    for (int b = 0; b < (a.uniform ? 1 : a.nimg); ++b) two = two || a.desc[b].k2 > 0;
+    const size_t lds = launch_lds(nmax, two);
+    const int groups = two && a.groups > 0 ? a.groups : 1;
+    auto pick = [&](auto stage2) {
+        constexpr bool TWO = decltype(stage2)::value;
+        return nmax <= 4 * kThreads ? select_kernel<4, TWO>
+               : nmax <= 10 * kThreads ? select_kernel<10, TWO> : select_kernel<kMaxSlots, TWO>;
+    };
+    auto kernel = two ? pick(std::true_type{}) : pick(std::false_type{});
     hipLaunchKernelGGL(kernel, dim3(a.nimg * groups), dim3(kThreads), lds, s, a);
     if (groups > 1) {
         hipLaunchKernelGGL(emit_kernel, dim3(a.nimg), dim3(kThreads), 0, s, a);

@@ -41,7 +41,7 @@ CASES += [([5000] * 4, 0.1), ([9001, 64, 1, 4200, 1024, 1025, 16384] * 2, 0.11),
 
 
 @pytest.mark.parametrize("shape", ["smooth", "padded", "clusters", "period", "sorted"])
-@pytest.mark.parametrize("lam", [0.0, 1 / 3, 0.9])
+@pytest.mark.parametrize("lam", [0.0, 1 / 3, 0.9, 1.0])
 def test_large_images_on_shaped_keys(shape, lam):
     import paper_2607_13500_amd as tr
     rng = np.random.default_rng(3)
