@@ -63,6 +63,8 @@ constexpr int kSample = 128;             // Stage II: samples that share out an 
 constexpr int kShareRem = 4096;          // Stage II: share images with this many remaining tokens
 constexpr int kListN = 2 * kShareRem;    // images below this have LDS for every token as a pair
 constexpr int kMaxSplitGroups = 64;      // most workgroups sharing the ranking of one large image
+static_assert((uint32_t)(kListN / 2) * (kListN / 2) > kCountFixed + kCountPer * kMaxSlots * kThreads,
+              "a bucket that the list cannot hold is sorted");
 static_assert(kMembers <= (uint32_t)kThreads, "one thread per listed Stage I member");
 static_assert((kMaxSplitGroups & (kMaxSplitGroups - 1)) == 0 && kMaxSplitGroups * 2 <= kSample,
               "two samples or more to a workgroup");
@@ -90,10 +92,10 @@ __host__ __device__ inline size_t align_up(size_t v, size_t a) { return (v + a -
 //                       u16[256][W] digit counts / offsets of the radix sort
 //   slots u32[8][W]     per-wavefront partial values, one row per use
 //   misc  u32[16]       broadcast words (kM*)
-//   list  list_bytes    the own tokens in bucket order: u64 (key << 32 | index)
-//                       if they fit, else u16 indices.  n < kListN: a
-//                       region of u64[n], else the bytes of ki (a share of a
-//                       large image is far smaller)
+//   list  list_bytes    the own tokens in bucket order, u64 (key << 32 | index).
+//                       n < kListN: a region of u64[n], else the bytes of ki
+//                       (a share of a large image is far smaller; an image that
+//                       one workgroup ranks alone is listed in parts)
 __host__ __device__ inline LdsLayout lds_layout(int n, bool two = true)
 {
     LdsLayout L;
@@ -936,17 +938,13 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
             slots[2 * kW + w] = rem_below;
         }
         __syncthreads();
-        cur[tid] = inc - c + sum_before(slots, w, lane);
+        const uint32_t start = inc - c + sum_before(slots, w, lane);
         const int m = (int)sum_before(slots, kW, lane);
         const uint32_t base = sum_before(slots + 2 * kW, kW, lane);
         const bool sorted = sum_before(slots + kW, kW, lane) > kCountFixed + kCountPer * (uint32_t)m;
+        H[tid] = start;     // bucket starts and cursors from here on
+        cur[tid] = start;
         __syncthreads();
-        // Both list forms: add the own tokens at their buckets' cursors, then a
-        // thread per listed token counts the smaller members of its bucket.
-        auto list_own = [&](auto put) {
-            for_own([&](int i) { put(atomicAdd(&cur[bucket_of(bk, ks[i], kBuckets)], 1u), ks[i], i); });
-            __syncthreads();
-        };
         if (sorted) {
             // the tokens left out (G = 1: X^imp, as it is)
             const int words = 2 * ((N + kWave - 1) / kWave);
@@ -962,26 +960,44 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
                                                reinterpret_cast<uint16_t*>(H), slots + 4 * kW, slots + 5 * kW);
             for (int j = tid; j < m; j += kThreads)
                 if (sp.picks(base + (uint32_t)j)) keep(order[j]);
-        } else if (8 * (size_t)m <= L.list_bytes) {
-            uint64_t* list = reinterpret_cast<uint64_t*>(smem + L.list);
-            list_own([&](uint32_t at, uint32_t key, int i) { list[at] = pair_of(key, (uint32_t)i); });
-            for (int j = tid; j < m; j += kThreads) {
-                const uint64_t me = list[j];
-                const int b = bucket_of(bk, (uint32_t)(me >> 32), kBuckets);
-                const uint32_t n = H[b];
-                if (sp.picks(base + rank_in(list, cur[b] - n, n, me))) keep((uint32_t)me);
-            }
         } else {
-            uint16_t* list = reinterpret_cast<uint16_t*>(ki);
-            list_own([&](uint32_t at, uint32_t, int i) { list[at] = (uint16_t)i; });
-            for (int j = tid; j < m; j += kThreads) {
-                const uint32_t i = list[j], key = ks[i];
-                const int b = bucket_of(bk, key, kBuckets);
-                const uint32_t end = cur[b], beg = end - H[b];
-                uint32_t r = beg;
-#pragma unroll 4
-                for (uint32_t p = beg; p < end; ++p) r += pair_of(ks[list[p]], list[p]) < pair_of(key, i) ? 1u : 0u;
-                if (sp.picks(base + r)) keep(i);
+            // The own tokens go to their buckets' cursors in the list, then a
+            // thread per listed token counts the smaller members of its bucket.
+            // PARTS: the buckets that start in [from, to), for the list holds
+            // no more (an image above kListN that one workgroup ranks alone:
+            // 17000 tokens in two parts 56 us, as one list of u16 indices 103).
+            uint64_t* list = reinterpret_cast<uint64_t*>(smem + L.list);
+            auto rank_part = [&](uint32_t from, uint32_t to, auto parts) {
+                constexpr bool PARTS = decltype(parts)::value;
+                for_own([&](int i) {
+                    const int b = bucket_of(bk, ks[i], kBuckets);
+                    if (PARTS && (H[b] < from || H[b] >= to)) return;
+                    list[atomicAdd(&cur[b], 1u) - from] = pair_of(ks[i], (uint32_t)i);
+                });
+                __syncthreads();
+                for (uint32_t j = from + (uint32_t)tid; j < to; j += kThreads) {
+                    const uint64_t me = list[j - from];
+                    const int b = bucket_of(bk, (uint32_t)(me >> 32), kBuckets);
+                    const uint32_t beg = H[b];
+                    if (sp.picks(base + from + rank_in(list, beg - from, cur[b] - beg, me))) keep((uint32_t)me);
+                }
+            };
+            const uint32_t cap = (uint32_t)(L.list_bytes / 8), all = (uint32_t)m;
+            if (all <= cap) {
+                rank_part(0u, all, std::false_type{});
+            } else {
+                for (uint32_t from = 0, to; from < all; from = to) {
+                    to = all;
+                    if (all - from > cap) {   // the last bucket start within the list's reach
+                        int b = 0;
+                        for (int step = kBuckets / 2; step; step >>= 1)
+                            if (H[b + step] <= from + cap) b += step;
+                        to = H[b];
+                        if (to <= from) break;   // a bucket that the list cannot hold: never (static_assert above)
+                    }
+                    rank_part(from, to, std::true_type{});
+                    __syncthreads();
+                }
             }
         }
     }

@@ -37,7 +37,7 @@ CASES = [([n], share) for n, share in
          [(1025, 0.3), (4095, 0.2), (4097, 0.001), (4608, 0.4), (8191, 0.3), (8193, 0.02), (10240, 0.5), (10241, 0.9),
           (18432, 0.0625), (18796, 0.01)]]
 CASES += [([5000] * 4, 0.1), ([9001, 64, 1, 4200, 1024, 1025, 16384] * 2, 0.11), ([4500] * 40, 0.2),
-          ([9000] * 130, 0.05)]
+          ([9000] * 130, 0.05), ([17000] * 129, 0.05)]
 
 
 @pytest.mark.parametrize("shape", ["smooth", "padded", "clusters", "period", "sorted"])
