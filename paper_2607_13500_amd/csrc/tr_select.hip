@@ -55,10 +55,10 @@ constexpr int kUnr = 4;                  // tokens per thread a pass reads befor
 constexpr int kBuckets = kThreads;       // buckets of a histogram (one per thread in the scan)
 constexpr uint32_t kMembers = 256;       // Stage I: list and rank the members of ranges this small
 // Stage II: own tokens are ranked by counting while the squares of their buckets'
-// sizes (the LDS reads) sum to at most kCountFixed + kCountPer for each of them:
-// 1500 tokens in two buckets of 750 took 38 us to count, and sorting takes
-// about 10 us for each thousand tokens.
-constexpr uint32_t kCountFixed = 150000, kCountPer = 300;
+// sizes (the LDS reads) sum to at most kCountFixed + kCountPer for each of them.
+// Counting takes 26 us for a million, sorting 5 us and 6.6 for each thousand
+// tokens (2880 tokens, 979 of them of one key, 958000: 39.7 us counted, 33.8 sorted).
+constexpr uint32_t kCountFixed = 50000, kCountPer = 250;
 constexpr int kSample = 128;             // Stage II: samples that share out an image
 constexpr int kShareRem = 4096;          // Stage II: share images with this many remaining tokens
 constexpr int kListN = 2 * kShareRem;    // images below this have LDS for every token as a pair
@@ -548,12 +548,17 @@ __device__ __forceinline__ void stage1_scan(uint32_t wave_below, uint32_t K1, ui
 
 // One round's histogram over the keys in LDS: tokens with lo <= v <= hi go to
 // bucket (v - lo) >> sh, those below lo are counted for the wavefront.  v is
-// the key, or (INDEX) the index of the tokens whose key is `only`.
+// the key, or (INDEX) the index of the tokens whose key is `only`, all of them in
+// buckets of 32.  Atomics of many lanes on one bucket run one after the other
+// (3600 tokens of one key: 3 us), so a range of one key is counted by ballots.
+constexpr int kIdxShift = 5;
+
 template <bool INDEX>
 __device__ uint32_t stage1_histogram(const uint32_t* ki, int N, uint32_t only, uint32_t lo, uint32_t hi, int sh,
                                      uint32_t* H)
 {
-    uint32_t nb = 0;
+    const int lane = threadIdx.x & (kWave - 1);
+    uint32_t nb = 0, one = 0;
     for_tokens(N, [&](int, int i0) {
         uint32_t k[kUnr];
         read_keys(ki, i0, N, k);
@@ -562,10 +567,20 @@ __device__ uint32_t stage1_histogram(const uint32_t* ki, int N, uint32_t only, u
             const int i = i0 + q * kThreads;
             const uint32_t v = INDEX ? (uint32_t)i : k[q];
             const bool have = i < N && (!INDEX || k[q] == only);
-            nb += (uint32_t)__popcll(__ballot(have && v < lo));
-            if (have && v - lo <= hi - lo) atomicAdd(&H[(v - lo) >> sh], 1u);
+            if constexpr (INDEX) {   // a tile's tokens fall into two buckets: lanes 0 and 32 count them
+                static_assert(kIdxShift == 5, "half a tile to a bucket");
+                const uint64_t m = __ballot(have);
+                const uint32_t n = lane < 32 ? (uint32_t)__popc((uint32_t)m) : (uint32_t)__popc((uint32_t)(m >> 32));
+                if ((lane & 31) == 0 && n) atomicAdd(&H[v >> kIdxShift], n);
+            } else {
+                const bool in = have && v - lo <= hi - lo;
+                nb += (uint32_t)__popcll(__ballot(have && v < lo));
+                if (lo == hi) one += (uint32_t)__popcll(__ballot(in));
+                else if (in) atomicAdd(&H[(v - lo) >> sh], 1u);
+            }
         }
     });
+    if (!INDEX && lane == 0 && one) atomicAdd(&H[0], one);
     return nb;
 }
 
@@ -614,8 +629,11 @@ __device__ __forceinline__ Boundary stage1_boundary(const uint32_t* ki, int N, u
     r.ilo = 0u;
     r.ihi = 0xffffffffu;
     r.tie = m > kMembers;
-    if (r.tie) {   // tokens of one key value: those of the lowest indices
-        constexpr int kIdxShift = 5;
+    if (r.tie && m == (uint32_t)N) {   // every key is equal: the first K1 tokens, no boundary left
+        r.need = 0u;
+        r.ilo = K1;
+        r.ihi = K1 - 1u;
+    } else if (r.tie) {   // tokens of one key value: those of the lowest indices
         static_assert(kMaxSlots * kThreads <= kBuckets << kIdxShift, "every index has a bucket");
         const uint32_t nb = stage1_histogram<true>(ki, N, lo, 0u, (uint32_t)N - 1u, kIdxShift, H);
         stage1_scan(nb, r.need, H, misc, row_b, row_c, below, inside);
@@ -664,7 +682,7 @@ __device__ __forceinline__ void second_pass_step(const uint32_t* ki, const uint3
         const bool valid = FULL || i < N;
         const uint64_t pi = pair_of(qi[q], (uint32_t)i), ps = pair_of(qs[q], (uint32_t)i);
         const bool imp = EXACT ? pi < imp_end : qi[q] < bd.lo;
-        const bool upto = EXACT ? pi <= mhi : qi[q] <= bd.hi;   // X^imp or a member
+        const bool upto = EXACT ? pi <= mhi : qi[q] < bd.hi + 1u;   // X^imp or a member
         const bool below = EXACT ? ps < sh.lo : qs[q] < klo;
         const bool under = EXACT ? sh.open || ps < sh.hi : qs[q] <= khi;
         const uint64_t vm = FULL ? ~0ull : __ballot(valid);
@@ -826,24 +844,33 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
 
     // ---- keys to LDS, the first range's histogram -----------------------------------
     uint32_t nlo_s = 0, hi_s = 0, wave_below = 0;
+    auto keep_keys = [&](auto single) {   // single: the range is one key, counted as in stage1_histogram
+        constexpr bool ONE = decltype(single)::value;
+        uint32_t one = 0;
 #pragma unroll
-    for (int u = 0; u < S; ++u) {
-        const int i = u * kThreads + tid;
-        if (i < N) {
-            const uint32_t qi = order_key(vi[u]);
-            ki[i] = qi;
-            if constexpr (TWO) {
-                const uint32_t qs = order_key(vs[u]);
-                ks[i] = qs;
-                nlo_s = max(nlo_s, ~qs);
-                hi_s = max(hi_s, qs);
-            }
-            if (staged) {
-                wave_below += (uint32_t)__popcll(__ballot(qi < lo));   // lane 0 is in every tile's ballot
-                if (qi - lo <= hi - lo) atomicAdd(&H[(qi - lo) >> sh], 1u);
+        for (int u = 0; u < S; ++u) {
+            const int i = u * kThreads + tid;
+            if (i < N) {
+                const uint32_t qi = order_key(vi[u]);
+                ki[i] = qi;
+                if constexpr (TWO) {
+                    const uint32_t qs = order_key(vs[u]);
+                    ks[i] = qs;
+                    nlo_s = max(nlo_s, ~qs);
+                    hi_s = max(hi_s, qs);
+                }
+                if (staged) {
+                    wave_below += (uint32_t)__popcll(__ballot(qi < lo));   // lane 0 is in every tile's ballot
+                    if constexpr (ONE) one += (uint32_t)__popcll(__ballot(qi == lo));
+                    else if (qi - lo <= hi - lo) atomicAdd(&H[(qi - lo) >> sh], 1u);
+                }
             }
         }
-    }
+        if (ONE && lane == 0 && one) atomicAdd(&H[0], one);
+    };
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(staged && lo == hi), 0))   // the same in every thread
+        keep_keys(std::true_type{});
+    else keep_keys(std::false_type{});
     if constexpr (TWO) {
         nlo_s = wave_max_u32(nlo_s);
         hi_s = wave_max_u32(hi_s);
@@ -866,7 +893,8 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
     // A share's end is a key, or a pair where the sampled key repeats (its
     // neighbours decide: the workgroups on both sides of it read the same).
     Share own_range{0ull, 0ull, !(split && part < G - 1)};
-    bool exact = !staged || bd.tie;
+    bool exact = staged ? bd.tie || bd.hi == 0xffffffffu : K1 > 0;
+    if (!staged) bd.hi = 0xffffffffu;   // hi + 1 = 0: no key is X^imp or a member
     auto share_end = [&](uint32_t r, uint64_t pair) {
         const uint32_t k = sorted_keys[r];
         const bool repeats = k == sorted_keys[r - 1] || k == sorted_keys[r + 1] || k == 0u;
@@ -926,7 +954,12 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
             for (uint32_t o = own; o; o &= o - 1u) f((__ffs((int)o) - 1) * kThreads + tid);
             if (extra >= 0) f(extra);
         };
-        for_own([&](int i) { atomicAdd(&H[bucket_of(bk, ks[i], kBuckets)], 1u); });
+        if (__builtin_expect(bk.mode == 2, 0)) {   // one key, one bucket
+            const uint32_t n = wave_sum_u32((uint32_t)__popc(own) + (extra >= 0 ? 1u : 0u));
+            if (lane == 0 && n) atomicAdd(&H[0], n);
+        } else {
+            for_own([&](int i) { atomicAdd(&H[bucket_of(bk, ks[i], kBuckets)], 1u); });
+        }
         __syncthreads();
         if (split && part == 0)
             for (int i = tid; i < (N + 31) / 32; i += kThreads) a.gimp[wbase + i] = bimp[i];
