@@ -57,6 +57,8 @@
 // accuracy for near-uniform rows.  The terms are summed in base-2 units
 // (e / ln 2 and g / ln 2), which saves a multiply per element; the row's sum
 // is scaled by ln 2 once.
+#include <type_traits>
+
 #include "tr_row.h"
 #include "tr_score.h"
 #include "tr_wave.h"
@@ -336,11 +338,14 @@ __device__ __noinline__ XRow x_reread(const char* row, int D, int lane)
 }
 
 // How a launch reads its rows.
-constexpr int kBurst = 0;   // UNR chunks of every tensor per lane at once
+constexpr int kBurst = 0;   // up to four chunks of every tensor per lane at once
 constexpr int kPaced = 1;   // one or two loads of a wavefront in flight (see launch_t)
 constexpr int kOdd = 2;     // as kBurst; rows that are no whole number of 16-byte chunks
 
-template <bool BF16, int UNR, int MODE, int READ>
+template <int N>
+using Int = std::integral_constant<int, N>;
+
+template <bool BF16, int MODE, int READ>
 __global__ __launch_bounds__(kWave) void score_kernel(ScoreArgs a)
 {
     using L = Layout<BF16>;
@@ -364,7 +369,8 @@ __global__ __launch_bounds__(kWave) void score_kernel(ScoreArgs a)
     // belongs to lane (index % 64) like any other and is its lane's last.
     const int nfx = kX ? a.D / V : 0, mx = kX && ODD ? a.D % V : 0;
     const int nfc = kC ? a.Dc / V : 0, mc = kC && ODD ? a.Dc % V : 0;
-    const int chunks = max(nfx + (mx ? 1 : 0), nfc + (mc ? 1 : 0));
+    // A column is 64 chunks, one to a lane.
+    const int colsx = (nfx + (mx ? 1 : 0) + kWave - 1) / kWave, colsc = (nfc + (mc ? 1 : 0) + kWave - 1) / kWave;
     const int endx = a.D * L::kEB - 16, endc = a.Dc * L::kEB - 16;   // a row's last 16 bytes
     const bool short_rows = ODD && ((kX && endx < 0) || (kC && endc < 0));
     // elements in the lanes' first chunks: the sample the shift c averages
@@ -397,26 +403,30 @@ __global__ __launch_bounds__(kWave) void score_kernel(ScoreArgs a)
         const float scale = fast_x ? binade_scale(c_raw) : 1.f;
         sh = make_shift(fast_x ? c_raw * scale : 0.f, scale);
     };
-    // Every load of a step is issued before anything waits: a lane past the
-    // row's end loads its last 16 bytes (the wavefront's lanes then ask for one
-    // address) instead of skipping the load.  Skipped loads kept their
+    // One step: UNR columns from column c0 on, of X (HX) and of X_pre and X_post
+    // (HC).  Every load of a step is issued before anything waits: a lane past
+    // the row's end loads its last 16 bytes (the wavefront's lanes then ask for
+    // one address) instead of skipping the load.  Skipped loads kept their
     // registers tied to the step before, so the loads went out one or two at a
     // time, each behind the one before.  The lane of a partial chunk gets it
     // at the end of those 16 bytes.
-    for (int j0 = 0; j0 < chunks; j0 += kWave * UNR) {   // same trip count for every lane
-        Raw rx[UNR], rp[UNR], rq[UNR];
+    auto step = [&](int c0, auto unr, auto has_x, auto has_c) __attribute__((always_inline)) {
+        constexpr int UNR = decltype(unr)::value;
+        constexpr bool HX = decltype(has_x)::value, HC = decltype(has_c)::value;
+        const int j0 = c0 * kWave;
+        [[maybe_unused]] Raw rx[UNR], rp[UNR], rq[UNR];
         if (!short_rows) {
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
                 const uint32_t off = (uint32_t)(j0 + lane + kWave * u) * 16;
-                if constexpr (kX) {
+                if constexpr (HX) {
                     pace();
                     rx[u] = load16(xr, min(off, (uint32_t)endx));
                 }
-                if constexpr (kC) {
+                if constexpr (HC) {
                     pace();
                     rp[u] = load16(pr, min(off, (uint32_t)endc));
-                    if constexpr (!kX) pace();
+                    if constexpr (!HX) pace();
                     rq[u] = load16(qr, min(off, (uint32_t)endc));
                 }
             }
@@ -424,15 +434,15 @@ __global__ __launch_bounds__(kWave) void score_kernel(ScoreArgs a)
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
                 const uint32_t off = (uint32_t)(j0 + lane + kWave * u) * 16;
-                if constexpr (kX) rx[u] = endx < 0 ? load_short<BF16>(xr, mx) : load16(xr, min(off, (uint32_t)endx));
-                if constexpr (kC) {
+                if constexpr (HX) rx[u] = endx < 0 ? load_short<BF16>(xr, mx) : load16(xr, min(off, (uint32_t)endx));
+                if constexpr (HC) {
                     rp[u] = endc < 0 ? load_short<BF16>(pr, mc) : load16(pr, min(off, (uint32_t)endc));
                     rq[u] = endc < 0 ? load_short<BF16>(qr, mc) : load16(qr, min(off, (uint32_t)endc));
                 }
             }
         }
         asm volatile("" ::: "memory");   // the loads stay here, none moves down to its use
-        if (kX && j0 == 0) {
+        if (HX && c0 == 0) {
             float v[V];
             int m = 0;
             v[0] = 0.f;
@@ -448,23 +458,48 @@ __global__ __launch_bounds__(kWave) void score_kernel(ScoreArgs a)
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const int ci = j0 + lane + kWave * u;
-            if (ci < nfx) {
+            if (HX && ci < nfx) {
                 float v[V];
                 unpack<BF16>(rx[u], v);
                 x_accumulate<kH1, V>(xa, v, V, sh);
             }
-            if (ci < nfc) c_chunk<BF16>(ca, rp[u], rq[u]);
+            if (HC && ci < nfc) c_chunk<BF16>(ca, rp[u], rq[u]);
             if constexpr (ODD) {
-                if (kX && mx && ci == nfx) {
+                if (HX && mx && ci == nfx) {
                     float v[V];
                     unpack<BF16>(endx < 0 ? rx[u] : tail_of<BF16>(rx[u], mx), v);
                     x_accumulate<kH1, V>(xa, v, mx, sh);
                 }
-                if (kC && mc && ci == nfc)
+                if (HC && mc && ci == nfc)
                     c_chunk<BF16>(ca, endc < 0 ? rp[u] : tail_of<BF16>(rp[u], mc),
                                   endc < 0 ? rq[u] : tail_of<BF16>(rq[u], mc));
             }
         }
+    };
+    // Columns from .. to - 1 in steps of four (paced: one) and a last one of
+    // exactly what is left: loads past the row, all of one address, still cost
+    // as much as others (300000 rows of 257 bf16 elements in steps of four 436 us).
+    auto run = [&](int from, int to, auto has_x, auto has_c) __attribute__((always_inline)) {
+        int c = from;
+        if constexpr (READ == kPaced) {
+            for (; c < to; ++c) step(c, Int<1>{}, has_x, has_c);
+        } else {
+            for (; to - c >= 4; c += 4) step(c, Int<4>{}, has_x, has_c);
+            const int rest = to - c;
+            if (rest == 2) step(c, Int<2>{}, has_x, has_c);
+            else if (rest == 1) step(c, Int<1>{}, has_x, has_c);
+            else if (rest == 3) step(c, Int<3>{}, has_x, has_c);
+        }
+    };
+    if constexpr (kX && kC) {
+        const int both = min(colsx, colsc);
+        run(0, both, std::true_type{}, std::true_type{});
+        if (colsx != colsc) {
+            if (colsx > both) run(both, colsx, std::true_type{}, std::false_type{});
+            else run(both, colsc, std::false_type{}, std::true_type{});
+        }
+    } else {
+        run(0, kX ? colsx : colsc, std::bool_constant<kX>{}, std::bool_constant<kC>{});
     }
 
     float sd = 0.f, sd2 = 0.f, s = 0.f;
@@ -575,12 +610,12 @@ hipError_t launch_t(const ScoreArgs& a, hipStream_t s)
     const int64_t row = (int64_t)(kX ? a.D : a.Dc) * kEB;
     const int64_t total = a.rows * row * (kX ? (kC ? 3 : 1) : 2);
     if ((kX && a.D % V) || (kC && a.Dc % V)) {
-        hipLaunchKernelGGL((score_kernel<BF16, 4, MODE, kOdd>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((score_kernel<BF16, MODE, kOdd>), grid, block, 0, s, a);
     } else if (row >= kPacedRow && total >= (kC ? kPacedBytes : kPacedBytesX) && !(kX && kC && a.D != a.Dc)) {
         const int pad = !kX ? 5440 : !kC ? 0 : total < kPacedLess ? 8192 : 10240;
-        hipLaunchKernelGGL((score_kernel<BF16, 1, MODE, kPaced>), grid, block, pad, s, a);
+        hipLaunchKernelGGL((score_kernel<BF16, MODE, kPaced>), grid, block, pad, s, a);
     } else {
-        hipLaunchKernelGGL((score_kernel<BF16, 4, MODE, kBurst>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((score_kernel<BF16, MODE, kBurst>), grid, block, 0, s, a);
     }
     return hipGetLastError();
 }
