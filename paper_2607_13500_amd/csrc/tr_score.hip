@@ -579,41 +579,79 @@ __global__ __launch_bounds__(kWave) void score_kernel(ScoreArgs a)
 // over the 256 CUs (measured 128 us vs 136 us with four-wavefront groups on
 // 64 x 576 x 4096 bf16 rows).
 //
-// Small launches are bound by the latency of their loads, so a wavefront
-// issues four chunks of every tensor at once (kBurst): 576 x 4096 bf16 rows
-// 12.1 -> 9.0 us a call, 20000 x 1152 33.5 -> 21.4 us, against loads that
-// waited for one another.  Large launches are bound by HBM, and there more
-// bytes in flight than the round trip needs (about 27 KB a CU) only queue
-// before the memory: 73728 x 4096 bf16 rows take 266 us with 32 wavefronts of
-// 12 KB in flight, 257 us with 12 of 3 KB, 253 us (7.17 TB/s) with 20 of 1-2
-// KB, 263 us with 8 of 3 KB.  So they are paced: a wavefront keeps X's chunk,
-// then X_pre's and X_post's in flight, with 20 wavefronts a CU (8 KB of unused
-// LDS each), or 16 from 1.5 GB on (46080 x 4096 rows, 1.1 GB: 158 us with 20,
-// 161 with 16; 73728 rows 255 and 253, 150000 rows 532 and 522); the states
-// alone one chunk at a time with 28 (166 against 174 us in bursts), X alone
-// with all 32 (86 against 89 us).  The line lies where
-// both measure the same: rows of 5 KB (3 KB rows: 118 paced against 123 us in
-// bursts, 4 KB 111 against 107, 2 KB 122 against 107) and 128 MB of reads (8 KB
-// rows: 75 MB 13.9 against 11.8 us, 113 MB 20.2 against 20.3, 226 MB 34.5
-// against 34.9; X alone from 512 MB on).
-constexpr int64_t kPacedRow = 5 << 10;
-constexpr int64_t kPacedBytes = 128 << 20, kPacedBytesX = 512 << 20;
-constexpr int64_t kPacedLess = (int64_t)3 << 29;
+// A wavefront issues up to four chunks of every tensor at once (kBurst), which
+// hides the latency that bounds small launches (576 x 4096 bf16 rows 12.1 -> 9.0
+// us a call against loads that waited for one another) and reaches HBM's rate in
+// most large ones.  Where a launch lasts for many rounds of wavefronts, more bytes
+// in flight than the round trip needs (about 27 KB a CU) only queue before the
+// memory, and paced reads are faster: a wavefront keeps X's chunk, then X_pre's
+// and X_post's in flight, and unused LDS limits the wavefronts of a CU.  A launch
+// of few rounds must not be paced: a CU without its share of wavefronts, in the
+// last round or with few rows at all, then waits for one chunk at a time.
+//
+// So the rule is one of rows (a round is 5120 of them with 20 wavefronts a CU),
+// and of row sizes, below which a row's few chunks are paced by nothing.  us,
+// burst against paced with that many wavefronts:
+//   X and states, 20: 8 KB rows (bf16) 48828 of them 177.4 / 170.2, 36621 131.5 /
+//     128.7, 24414 90.8 / 90.7; 6 KB 48828 133.4 / 129.4; 12 KB 32552 174.8 / 182.2;
+//     3 KB 130208 181.8 / 176.0, 32552 46.9 / 48.5; 2 KB 195312 183.6 / 189.3; Shannon,
+//     5 KB 58593 136.9 / 134.6, 4 KB 73242 134.1 / 135.9, 3 KB 97656 136.5 / 145.5.
+//   16 wavefronts from 1.6 GB on, for rows of 8 KB: 97656 336.9 (20) / 335.1 (16), fp32
+//     12 KB 65104 342.8 / 335.3; from 2 GB on with fewer rows too, 24414 fp32 rows
+//     of 32 KB 353.7 (burst) / 343.6.  Shannon over bf16 rows has more to compute
+//     and stays at 20: 97656 341.5 (20) / 352.3 (16).
+//   States alone, 28: 8 KB 146484 355.1 / 338.7, 36621 88.2 / 87.3, 18310 44.5 / 44.5,
+//     9155 22.7 / 26.9.
+//   X alone, all 32: 8 KB 146484 179.2 / 173.8, 73242 91.2 / 89.4, 36621 46.9 / 48.2;
+//     Shannon, 3 KB 195312 185.9 / 167.2, 8 KB 36621 75.4 / 80.3.
+//   X and states or states alone, 2 KB rows, all 32 (no pace but the chunk's own):
+//     states 585937 362.7 / 340.0, 146484 87.0 / 87.6.
+//   X and states of different widths, 28, from 1 GB on (columns that one of them
+//     has alone are read one chunk at a time, which 20 wavefronts are too few for:
+//     97656 rows of 4096 and 1024 bf16 181.6 in bursts, 190.4 with 20, 176.2 with 28):
+//     1024 and 4096 bf16 130208 365 / 346, 32552 90.5 / 92.4; Shannon over bf16 rows
+//     wider than the states stays in bursts (97656 of 4096 and 1024 240 / 239, 73242
+//     of 4096 and 2048 196 / 200).
+constexpr int64_t kManyRows = 35840;   // seven rounds
+
+// LDS bytes a workgroup of a paced launch asks for (which set the wavefronts of a
+// CU: 8 KB 20, 10 KB 16, 5.3 KB 28, none 32), or -1: not paced.
+template <bool BF16, int MODE>
+int paced_lds(int64_t rows, int64_t D, int64_t Dc)
+{
+    constexpr int kEB = Layout<BF16>::kEB;
+    constexpr bool kX = (MODE & kScoreImp) != 0, kC = (MODE & kScoreSim) != 0, kH1 = (MODE & kScoreShannon) != 0;
+    constexpr int k20 = 8192, k16 = 10240, k28 = 5440, k32 = 0;
+    constexpr int64_t kKB = 1 << 10, kMB = 1 << 20;
+    const int64_t row_bytes = (kX ? D : Dc) * kEB, total = rows * ((kX ? D : 0) + (kC ? 2 * Dc : 0)) * kEB;
+    if (kX && kC && D != Dc) {
+        const bool many = rows >= kManyRows && total >= 1000000000 && (D > Dc ? D : Dc) * kEB >= 4 * kKB;
+        return many && !(kH1 && BF16 && D > Dc) ? k28 : -1;
+    }
+    if (!kC) {
+        if (kH1) return rows >= 40960 && row_bytes >= 2 * kKB ? k32 : -1;
+        return rows >= 49152 && row_bytes >= 6 * kKB && total >= 512 * kMB ? k32 : -1;
+    }
+    if (!kH1 && row_bytes >= 2 * kKB && row_bytes < 3 * kKB) return rows >= 150000 ? k32 : -1;
+    if (!kX) return rows >= kManyRows && row_bytes >= 3 * kKB && total >= 512 * kMB ? k28 : -1;
+    const bool wide = row_bytes >= 8 * kKB && !(kH1 && BF16);
+    if (wide && total >= 2000000000 && rows >= 12000) return k16;
+    if (rows < kManyRows || row_bytes < (kH1 ? 5 : 3) * kKB) return -1;
+    return wide && total >= 1600000000 ? k16 : k20;
+}
 
 template <bool BF16, int MODE>
 hipError_t launch_t(const ScoreArgs& a, hipStream_t s)
 {
     if (a.rows <= 0) return hipSuccess;
-    constexpr int V = Layout<BF16>::kV, kEB = Layout<BF16>::kEB;
+    constexpr int V = Layout<BF16>::kV;
     constexpr bool kX = (MODE & kScoreImp) != 0, kC = (MODE & kScoreSim) != 0;
     const dim3 grid((unsigned)a.rows), block(kWave);
-    const int64_t row = (int64_t)(kX ? a.D : a.Dc) * kEB;
-    const int64_t total = a.rows * row * (kX ? (kC ? 3 : 1) : 2);
+    const int lds = paced_lds<BF16, MODE>(a.rows, a.D, a.Dc);
     if ((kX && a.D % V) || (kC && a.Dc % V)) {
         hipLaunchKernelGGL((score_kernel<BF16, MODE, kOdd>), grid, block, 0, s, a);
-    } else if (row >= kPacedRow && total >= (kC ? kPacedBytes : kPacedBytesX) && !(kX && kC && a.D != a.Dc)) {
-        const int pad = !kX ? 5440 : !kC ? 0 : total < kPacedLess ? 8192 : 10240;
-        hipLaunchKernelGGL((score_kernel<BF16, MODE, kPaced>), grid, block, pad, s, a);
+    } else if (lds >= 0) {
+        hipLaunchKernelGGL((score_kernel<BF16, MODE, kPaced>), grid, block, lds, s, a);
     } else {
         hipLaunchKernelGGL((score_kernel<BF16, MODE, kBurst>), grid, block, 0, s, a);
     }

@@ -2,8 +2,6 @@
 columns of 64 16-byte chunks, whole and partial last chunks, X and the states of
 different widths, rows below one chunk; and launches large enough to be paced,
 which must give each row the bits it gets in a small one."""
-import math
-
 import numpy as np
 import pytest
 import torch
@@ -61,3 +59,41 @@ def test_every_number_of_columns(dtype, shannon):
     for D, Dc in ((1, 1), (2, 7), (7, 2), (3, 4 * col), (4 * col, 5), (col, 8 * col), (8 * col, col), (3 * col + 8, 5 * col),
                   (6 * col, 2 * col + 1), (2 * col + 1, 6 * col), (9 * col, 4 * col + 3), (4, 4), (8, 8), (9, 17)):
         check(D, Dc, dtype, shannon)
+
+
+# launches that each rule paces: rows, D (and Dc), dtype, what is read
+PACED = [(61000, (1024, 4096), BF, "xc"), (61008, (3584, 3072), F4, "xch"), (36864, 4096, BF, "xc"), (130000, 1536, BF, "xc"), (98304, 4096, BF, "xc"), (12400, 16384, F4, "xc"), (150016, 1024, BF, "xc"),
+         (49152, 2560, BF, "xch"), (98304, 4096, BF, "xch"), (66000, 2048, F4, "xch"), (49160, 6144, BF, "x"), (41000, 1024, BF, "xh"),
+         (41000, 2048, F4, "xh"), (36864, 4096, BF, "c"), (151000, 512, F4, "c")]
+
+
+@pytest.mark.parametrize("rows,D,dtype,read", PACED)
+def test_a_row_scores_alike_in_launches_of_any_size(rows, D, dtype, read):
+    """The bits of a row's scores in a large (paced) launch are those it gets in a
+    launch of 300 rows, and those of the launches that read X or the states alone."""
+    import paper_2607_13500_amd as tr
+    print("[case] paced", rows, D, dtype, read, flush=True)
+    D, Dc = D if isinstance(D, tuple) else (D, D)
+    g = torch.Generator(device=DEV).manual_seed(rows + D)
+    T = [torch.empty(rows, d, dtype=dtype, device=DEV) if k in read else None for k, d in zip("xcc", (D, Dc, Dc))]
+    for t in T:
+        if t is not None:
+            for part in t.split(8192):
+                part.copy_(torch.randn(part.shape, generator=g, device=DEV))
+            t[5], t[rows - 2], t[rows // 2] = 0, t[rows - 2] * 2.0 ** -70, t[rows // 2] * 2.0 ** 66
+    r = tr.Reducer(D, Dc, dtype, max_images=1, max_tokens=rows, max_N=1, shannon="h" in read)
+    whole = r.score(*T, want_h2=True)
+    for at in (0, rows // 2 - 150, rows - 300):
+        some = [None if t is None else t[at:at + 300] for t in T]
+        got = [r.score(*some, want_h2=True)]
+        if "x" in read and "c" in read:
+            got.append(r.score(some[0], None, None, want_h2=True))
+            got.append(r.score(None, some[1], some[2]))
+        for res in got:
+            for w, v in zip(whole, res):
+                assert v is None or torch.equal(w[at:at + 300], v)
+    if "x" in read and "c" in read:
+        for alone in (r.score(T[0], None, None, want_h2=True), r.score(None, T[1], T[2])):
+            for w, v in zip(whole, alone):
+                assert v is None or torch.equal(w, v)
+    r.close()
