@@ -90,26 +90,45 @@ def test_gemm_gathered_rows(N):
     r.close()
 
 
-@pytest.mark.parametrize("tile_rows", [None, 128, 192, 256])
-def test_gemm_tilings_agree_bit_for_bit(tile_rows, monkeypatch):
-    """Products with N % 256 == 0 and N % 256 == 128 run the same MFMA sequence
-    for every output element, so the columns they share are bit-identical,
-    plain and gathered, at every tile height (TR_GEMM_TILE_ROWS pins it; None
-    leaves it to the model)."""
-    if tile_rows is not None:
-        monkeypatch.setenv("TR_GEMM_TILE_ROWS", str(tile_rows))
-    say("gemm wide vs narrow 1000 x 512/384 x 1024, tile rows", tile_rows)
+def far_rows(A, ld=1 << 22):
+    """The same matrix with rows 2^22 elements apart: beyond the buffer offsets of
+    the tiled kernel, so the kernel with 64-bit addresses takes it."""
+    wide = torch.empty((A.shape[0] - 1) * ld + A.shape[1], dtype=A.dtype, device=DEV).as_strided(A.shape, (ld, 1))
+    wide.copy_(A)
+    return wide
+
+
+@pytest.mark.parametrize("M,N,K", [(300, 512, 1024), (193, 384, 192), (65, 128, 64)])
+def test_gemm_tilings_agree_bit_for_bit(M, N, K, monkeypatch):
+    """Every tile height (TR_GEMM_TILE_ROWS pins it; None leaves it to the model)
+    and the kernel with 64-bit addresses give every output element the same MFMA
+    sequence, so the products are bit-identical: plain, gathered, with the cosine
+    epilogue, and on the columns that a narrower product shares."""
+    say("gemm tilings", M, N, K)
     g = torch.Generator().manual_seed(11)
-    A = randn_bf16(g, 1000, 1024).to(DEV)
-    B = randn_bf16(g, 512, 1024).to(DEV)
-    rows = torch.randint(-2, 1003, (600,), generator=g, dtype=torch.int32).to(DEV)
-    r = reducer()
-    wide, narrow = r.gemm(A, B), r.gemm(A, B[:384])
-    gw, gn = r.gemm(A, B, rows=rows), r.gemm(A, B[:384], rows=rows)
-    torch.cuda.synchronize()
-    assert torch.equal(wide[:, :384].view(torch.int16), narrow.view(torch.int16))
-    assert torch.equal(gw[:, :384].view(torch.int16), gn.view(torch.int16))
-    r.close()
+    A, B, P = randn_bf16(g, M, K).to(DEV), randn_bf16(g, N, K).to(DEV), randn_bf16(g, M, N).to(DEV)
+    rows = torch.randint(-2, M + 3, (M + 40,), generator=g, dtype=torch.int32).to(DEV)
+    far = far_rows(A)
+
+    def products(tile_rows, A):
+        if tile_rows is None:
+            monkeypatch.delenv("TR_GEMM_TILE_ROWS", raising=False)
+        else:
+            monkeypatch.setenv("TR_GEMM_TILE_ROWS", str(tile_rows))
+        r = reducer(D=N, Dc=N, max_tokens=M)
+        post, s = r.mlp_out_cos(A, B, P)
+        out = [r.gemm(A, B), r.gemm(A, B, rows=rows), post, r.gemm(A, B[:128])]
+        torch.cuda.synchronize()
+        r.close()
+        return [t.view(torch.int16) for t in out], s
+
+    first, s0 = products(256, A)
+    assert torch.equal(first[0], first[2]) and torch.equal(first[0][:, :128], first[3])
+    for tile_rows, a in ((192, A), (128, A), (None, A), (None, far)):
+        got, s = products(tile_rows, a)
+        for x, y in zip(first, got):
+            assert torch.equal(x, y), tile_rows
+        assert (s - s0).abs().max().item() <= 2e-6     # the sums' order differs from tile to tile
 
 
 def test_gemm_rejects_unsupported_shapes():
@@ -140,8 +159,8 @@ def test_mlp_out_cos_parity(M, Dc, Hd):
 
 @pytest.mark.parametrize("tile_rows", [128, 192, 256])
 def test_mlp_out_cos_parity_each_tile_height(tile_rows, monkeypatch):
-    """The cosine epilogue stages P through LDS by 128-row halves; 192-row
-    tiles split a wavefront's rows across both stages."""
+    """The cosine epilogue of each tile height: a wavefront holds 64, 96 or 128
+    rows of a tile, whose sums go through its own LDS rows."""
     monkeypatch.setenv("TR_GEMM_TILE_ROWS", str(tile_rows))
     run_mlp_out_cos_parity(1000, 512, 256)
 

@@ -32,12 +32,13 @@ def keys_of(shape, n, rng):
 
 
 # one image up to the sizes at which the loads, the list's place and the sharing
-# change; then batches that give an image 64, 16, 4 workgroups and one
+# change; then batches whose shared images (4096 remaining tokens or more, at every
+# lambda) get 64, 16, 8, 2 workgroups and one of 256 compute units, and ragged ones
 CASES = [([n], share) for n, share in
          [(1025, 0.3), (4095, 0.2), (4097, 0.001), (4608, 0.4), (8191, 0.3), (8193, 0.02), (10240, 0.5), (10241, 0.9),
           (18432, 0.0625), (18796, 0.01)]]
-CASES += [([5000] * 4, 0.1), ([9001, 64, 1, 4200, 1024, 1025, 16384] * 2, 0.11), ([4500] * 40, 0.2),
-          ([9000] * 130, 0.05), ([17000] * 129, 0.05)]
+CASES += [([9000] * b, 0.05) for b in (4, 12, 24, 100, 130)]
+CASES += [([5000] * 4, 0.1), ([9001, 64, 1, 4200, 1024, 1025, 16384] * 2, 0.11), ([4500] * 40, 0.2), ([17000] * 129, 0.05)]
 
 
 @pytest.mark.parametrize("shape", ["smooth", "padded", "clusters", "period", "sorted"])
