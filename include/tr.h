@@ -60,9 +60,8 @@
  *
  * Alignment: every tensor base must be aligned to its element size (2 bytes
  * for bf16, 4 for fp32 and for the int32 / float outputs); a base that is not
- * is an unsupported alignment, TR_EUNSUPPORTED.  Beyond that, 16-byte aligned
- * bases and row pitches take the vector path and others a scalar path with
- * bit-identical results.
+ * is an unsupported alignment, TR_EUNSUPPORTED.  Beyond that rows may start
+ * anywhere: a row's scores and copies do not depend on where it starts.
  */
 #ifndef TR_H
 #define TR_H
@@ -217,8 +216,9 @@ tr_status tr_select(tr_ctx* ctx, const float* key_imp, const float* key_s,
  * be 16-byte aligned (else TR_EINVAL).  Every tiling the library picks for a
  * shape gives the same bits (one fp32 accumulation order per element).  The
  * environment variable TR_GEMM_TILE_ROWS = 128, 192 or 256, read by
- * tr_create, pins the tile height of the kernel used for operands below 2 GB
- * (otherwise the height that fills the CUs best is taken). */
+ * tr_create, pins the tile height of the kernel used while a tile's rows (of a
+ * gathered A, all its rows) span less than 2 GB (otherwise the height that fills
+ * the CUs best is taken). */
 tr_status tr_gemm_bf16(tr_ctx* ctx, const void* A, int64_t lda,
                        const int32_t* a_rows, int64_t a_row_count,
                        const void* B, int64_t ldb, void* C, int64_t ldc,

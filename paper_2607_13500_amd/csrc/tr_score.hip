@@ -596,10 +596,11 @@ __global__ __launch_bounds__(kWave) void score_kernel(ScoreArgs a)
 //     128.7, 24414 90.8 / 90.7; 6 KB 48828 133.4 / 129.4; 12 KB 32552 174.8 / 182.2;
 //     3 KB 130208 181.8 / 176.0, 32552 46.9 / 48.5; 2 KB 195312 183.6 / 189.3; Shannon,
 //     5 KB 58593 136.9 / 134.6, 4 KB 73242 134.1 / 135.9, 3 KB 97656 136.5 / 145.5.
-//   16 wavefronts from 1.6 GB on, for rows of 7 KB: 262144 829.9 (20) / 819.4 (16), 8 KB
-//     97656 336.9 / 335.1, fp32 12 KB 65104 342.8 / 335.3, 3 KB 130208 180.8 / 190.8; from 2 GB on with fewer rows too, 24414 fp32 rows
-//     of 32 KB 353.7 (burst) / 343.6.  Shannon over bf16 rows has more to compute
-//     and stays at 20: 97656 341.5 (20) / 352.3 (16).
+//   16 wavefronts from 1.6 GB on, for rows of 7 KB: 262144 829.9 (20) / 819.4 (16),
+//     8 KB 97656 336.9 / 335.1, fp32 12 KB 65104 342.8 / 335.3, 3 KB 130208 180.8 /
+//     190.8; from 2 GB on with fewer rows too, 24414 fp32 rows of 32 KB 353.7 (burst)
+//     / 343.6.  Shannon over bf16 rows has more to compute and stays at 20: 97656
+//     341.5 (20) / 352.3 (16).
 //   States alone, 28: 8 KB 146484 355.1 / 338.7, 36621 88.2 / 87.3, 18310 44.5 / 44.5,
 //     9155 22.7 / 26.9.
 //   X alone, all 32: 8 KB 146484 179.2 / 173.8, 73242 91.2 / 89.4, 36621 46.9 / 48.2;

@@ -22,7 +22,8 @@
 // from 64 sampled keys around rank 64 K1 / N (a miss costs rounds over the side
 // it names), and its histogram is taken as the keys arrive from memory.  At
 // kMembers keys or fewer the range is left to the next pass; when one key value
-// is left, the indices of its tokens are narrowed the same way.
+// is left, the indices of its tokens are narrowed the same way (when all keys
+// are equal, X^imp is the first K1 tokens).
 //
 // The second pass marks the keys below the range as X^imp, lists the range's
 // members (ranked by counting: X^imp or not) and finds the workgroup's own
@@ -34,9 +35,10 @@
 // non-decreasing in the key) and listed in bucket order, and a thread per listed
 // token counts the members of its bucket smaller in (key, index) order.  Its
 // rank in X^rem is the three counts' sum: exact, whatever the samples.  If
-// many tokens share a bucket (kCountFixed) the own tokens are sorted instead, by a stable LSD radix sort of 16-bit indices (ordered compaction
-// first, digits looked up by index, per-wavefront scatter offsets, passes over
-// constant bytes skipped).
+// many tokens share a bucket (kCountFixed) the own tokens are sorted instead, by
+// a stable LSD radix sort of 16-bit indices (ordered compaction first, digits
+// looked up by index, per-wavefront scatter offsets, passes over constant bytes
+// skipped).
 //
 // In the output step every wavefront owns a contiguous, 64-aligned range of
 // tokens; all results are exact and deterministic.
@@ -736,20 +738,16 @@ __device__ __forceinline__ int sample_token(int k, int N)
 //
 // Bound by the latency of its phases (a dozen barriers of sixteen wavefronts, a
 // round trip to memory) and by VALU issue in the two passes over all tokens.
-// A workgroup of the 4 x 18432 clips, us from its start, against the kernel that
+// A workgroup of the 4 x 18432 clips, us from its start, against a kernel that
 // bucketed every key from LDS and all of X^rem in every workgroup: samples ranked
-// 2.7, keys and first histogram 6.5 (6.6), boundary 8.6 (12), second pass 12-13
-// (16), own tokens' histogram and scan 14 (20), ranked 15 (23).  Calls: 4 x
-// 18432 tokens 320 -> 301 us, 32 images of up to 16384 969 -> 944, 16 x 2880 193
-// -> 189, selection alone of 24 images of up to 18000 tokens 39 -> 28 (at lambda =
-// 1, one workgroup an image, images of 4089 to 8162 tokens: 2 us slower).  Tried
-// and left out: the keys in registers instead of LDS (19 + 19 a thread, every
-// pass unrolled over them: 10000 instructions, not run); comparisons of (key,
-// index) pairs in every pass (second pass 1.2 us more); variants of the second
-// pass without Stage II for K2 = 0 (one more copy of its code: every pass 1 us
-// slower, K2 = 0 no faster); value buckets over sampled quantiles with the tails
-// clamped into the end buckets (a tail of 3 % of 18000 tokens went to the radix
-// sort: 56 us).
+// 2.9, keys and first histogram 6.9 (6.6), boundary 9.1 (12), second pass 13-14
+// (16), own tokens' histogram and scan 15-16 (20), ranked 16-18 (23).  Selection
+// alone of 24 images of up to 18000 tokens: 39 -> 28 us.  Tried and left out: the
+// keys in registers instead of LDS (19 + 19 a thread, every pass unrolled over
+// them: 10000 instructions, not run); comparisons of (key, index) pairs in every
+// pass (second pass 1.2 us more); value buckets over sampled quantiles with the
+// tails clamped into the end buckets (a tail of 3 % of 18000 tokens went to the
+// radix sort: 56 us).
 //
 // Without TWO no image of the launch has a Stage II (K1 = K, as at lambda = 1):
 // nothing of its keys is loaded, kept or ranked.
@@ -1043,7 +1041,8 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a)
 
 // Output of the images select_kernel shared between workgroups: X^imp and the
 // picks from the global bitmaps (which are cleared for the next call), then
-// the ordered output (each lane reads its own tile's words).  One workgroup per image of the launch.
+// the ordered output (each lane reads its own tile's words).  One workgroup per
+// image of the launch.
 __global__ __launch_bounds__(kThreads) void emit_kernel(SelectArgs a)
 {
     __shared__ uint32_t row[kW];
@@ -1074,9 +1073,9 @@ __global__ __launch_bounds__(kThreads) void emit_kernel(SelectArgs a)
 // Both stages are ranked in the same passes.  Every token gets its exact rank
 // in (Stage II key, index) order among all N tokens, and its place relative
 // to K1 in (Stage I key, index) order (counted exactly only inside the bucket
-// that holds the K1 boundary); X^imp is the places below K1, and a token of X^rem ranks in X^rem as
-// its Stage II rank minus the X^imp tokens ranked below it (read from a
-// bitmap of X^imp in Stage II rank order), which decides the stride picks.
+// that holds the K1 boundary); X^imp is the places below K1, and a token of X^rem
+// ranks in X^rem as its Stage II rank minus the X^imp tokens ranked below it (read
+// from a bitmap of X^imp in Stage II rank order), which decides the stride picks.
 // Ranks come from value buckets and exact counting inside a bucket: bucket =
 // clamp(floor((v - lo) nb / (hi - lo)), 0, nb - 1) is non-decreasing in the
 // key, so rank = (tokens in lower buckets) + (members of the token's bucket
