@@ -232,7 +232,9 @@ tr_status tr_gemm_bf16(tr_ctx* ctx, const void* A, int64_t lda,
  *                   registers
  * so the Stage II key is ready without another pass over X_pre or X_post.
  * It is Eq. (6) of the X_post the caller receives, as tr_reduce's scoring
- * computes it up to the order of the fp32 sums.
+ * computes it up to the order of the fp32 sums.  X_post may be X_pre itself: a
+ * row whose squared norms lie outside [2^-60, FLT_MAX] then keeps the cosine of
+ * its unscaled fp32 sums (0 where they underflow), as x' is gone.
  *   Hact   device bf16 [M, Hd] hidden activations sigma(W1 x'), row stride ldh
  *   W2     device bf16 [Dc, Hd], row stride ldw
  *   X_pre  device bf16 [M, Dc] (x'), X_post device bf16 [M, Dc] (written)

@@ -184,9 +184,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a)
                 const int n = n0 + wn * 64 + j * 32 + (lane & 31);
                 const uint16_t cb = to_bf16(acc[i][j][v]);
                 const float c = bf16_lo(cb);   // the value stored
+                [[maybe_unused]] float p = 0.f;
+                if constexpr (COS)   // before C is stored, which may be P
+                    if (ok) p = bf16_lo(reinterpret_cast<const uint16_t*>(a.P)[(int64_t)m * a.ldp + n]);
                 if (ok) C[(int64_t)m * a.ldc + n] = cb;
                 if constexpr (COS) {
-                    const float p = ok ? bf16_lo(reinterpret_cast<const uint16_t*>(a.P)[(int64_t)m * a.ldp + n]) : 0.f;
                     dot = fmaf(p, c, dot);
                     pp = fmaf(p, p, pp);
                     cc = fmaf(c, c, cc);
@@ -654,7 +656,9 @@ __global__ __launch_bounds__(kPThreads, 1) void gemm_large_kernel(GemmArgs a)
 // whose squared norms leave the accepted range (states of magnitude 2^-75 to
 // 2^-30, whose products underflow in part, or beyond 2^63) is read again by the
 // wavefront, each vector scaled by its own maximum.  A wavefront takes few rows
-// because it reads them again one by one.
+// because it reads them again one by one.  Without a.P (C was stored over P) such
+// a row keeps the cosine of its sums as they are, or 0 where a squared norm is so
+// small that mark_underflow may have made it.
 constexpr int kFinishRows = 16;   // rows of a wavefront
 
 __global__ __launch_bounds__(256) void cos_finish_kernel(GemmArgs a, int cols)
@@ -672,8 +676,8 @@ __global__ __launch_bounds__(256) void cos_finish_kernel(GemmArgs a, int cols)
             n1 += p[3 * c + 1];
             n2 += p[3 * c + 2];
         }
-        if (cos_in_range(n1, n2)) v = dot / (sqrtf(n1) * sqrtf(n2));
-        else again = n1 != 0.f && n2 != 0.f;
+        if (cos_in_range(n1, n2) || (!a.P && n1 >= 0x1p-100f && n2 >= 0x1p-100f)) v = dot / (sqrtf(n1) * sqrtf(n2));
+        else again = a.P && n1 != 0.f && n2 != 0.f;
     }
     for (uint64_t left = __ballot(again); left; left &= left - 1) {
         const int l = __ffsll((long long)left) - 1;
@@ -804,8 +808,11 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !cos) return e;
+    GemmArgs f = a;
+    const char *p = static_cast<const char*>(a.P), *c = static_cast<const char*>(a.C);
+    if (p < c + (int64_t)a.M * a.ldc * 2 && c < p + (int64_t)a.M * a.ldp * 2) f.P = nullptr;   // C lies over P
     constexpr int kRows = kFinishRows * (256 / kWave);
-    hipLaunchKernelGGL(cos_finish_kernel, dim3((unsigned)(((int64_t)a.M + kRows - 1) / kRows)), dim3(256), 0, s, a,
+    hipLaunchKernelGGL(cos_finish_kernel, dim3((unsigned)(((int64_t)a.M + kRows - 1) / kRows)), dim3(256), 0, s, f,
                        (a.N + bn - 1) / bn);
     return hipGetLastError();
 }

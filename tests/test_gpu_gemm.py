@@ -228,6 +228,34 @@ def test_mlp_out_cos_at_any_magnitude(ldh):
     r.close()
 
 
+@pytest.mark.parametrize("ldh", [None, 1 << 22])
+def test_mlp_out_cos_in_place(ldh):
+    """X_post stored over X_pre: rows of ordinary magnitude get the cosine of the
+    x' that was there, bit for bit; rows whose squares underflow must not be
+    compared with themselves (s = 1) but get 0."""
+    M, Dc, Hd = 40, 384, 128
+    say("mlp_out_cos in place", M, Dc, Hd, "ldh", ldh)
+    Xpre, H, W2 = mlp_inputs(M, Dc, Hd, 33)
+    Xpre[5] = (Xpre[5].double() * 2.0 ** -80).to(torch.bfloat16)
+    H[9] = (H[9].double() * 2.0 ** -80).to(torch.bfloat16)
+    r = reducer(D=Dc, Dc=Dc, max_tokens=M)
+    Hd_dev = H.to(DEV)
+    if ldh is not None:
+        wide = torch.empty((M - 1) * ldh + Hd, dtype=torch.bfloat16, device=DEV).as_strided((M, Hd), (ldh, 1))
+        wide.copy_(Hd_dev)
+        Hd_dev = wide
+    Xd = Xpre.to(DEV)
+    Xpost, s = r.mlp_out_cos(Hd_dev, W2.to(DEV), Xd)
+    same, s_in = r.mlp_out_cos(Hd_dev, W2.to(DEV), Xd, out=Xd)
+    torch.cuda.synchronize()
+    assert same.data_ptr() == Xd.data_ptr() and torch.equal(same, Xpost)
+    tiny = torch.zeros(M, dtype=torch.bool, device=DEV)
+    tiny[[5, 9]] = True
+    assert torch.equal(s_in[~tiny], s[~tiny])
+    assert torch.all(s_in[tiny] == 0.0)
+    r.close()
+
+
 def test_fused_mlp_module_parity():
     """Stage II key from the fused epilogue, Stage I from X: the module's
     selection against the oracle's (H2 of X, cos(x', x'') on the stored x''),
