@@ -58,9 +58,11 @@ constexpr int kBuckets = kThreads;       // buckets of a histogram (one per thre
 constexpr uint32_t kMembers = 256;       // Stage I: list and rank the members of ranges this small
 // Stage II: own tokens are ranked by counting while the squares of their buckets'
 // sizes (the LDS reads) sum to at most kCountFixed + kCountPer for each of them.
-// Counting takes 26 us for a million, sorting 5 us and 6.6 for each thousand
-// tokens (2880 tokens, 979 of them of one key, 958000: 39.7 us counted, 33.8 sorted).
-constexpr uint32_t kCountFixed = 50000, kCountPer = 250;
+// us of a selection of 16 images counted / sorted, by tokens and crowded buckets: 1500,
+// one of 450 19.9 / 23.4, of 600 24.6 / 23.5; 2880, one of 600 26.1 / 33.7, of 1000 60.1
+// / 33.9, four of 250 23.7 / 33.5, of 350 36.0 / 33.7; 4000, one of 600 27.6 / 41.0, of
+// 1000 61.4 / 41.2, four of 250 33.7 / 41.0, of 450 52.8 / 41.2.
+constexpr uint32_t kCountFixed = 100000, kCountPer = 120;
 constexpr int kSample = 128;             // Stage II: samples that share out an image
 constexpr int kShareRem = 4096;          // Stage II: share images with this many remaining tokens
 constexpr int kListN = 2 * kShareRem;    // images below this have LDS for every token as a pair
